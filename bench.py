@@ -69,17 +69,17 @@ MLP_TRANS_PER_PAIR = 2 * 4 * 64   # SiLU of 4 x 64 hidden units: one exp and one
 # profiles/cone256_traffic_counters.md.  Valid only for the kernel sources they
 # were measured on (SHA-256 over QUAD_SOURCES); otherwise reported as null.
 QUAD_SOURCES = ["csrc/ss_kernels.hip", "csrc/ss_math.hpp", "csrc/ss_traverse.hpp", "csrc/ss_kernels.hpp"]
-TRAFFIC_SHA256 = "369c6360167dcf2aa49bd385ba21713a13c9bf62f635122478f66696ae4d78ea"
+TRAFFIC_SHA256 = "88892611331cb2c1d1e55582ebdeccd00b5bb9e30f02497ee01b64cbb2884731"
 TRAFFIC_BYTES = {  # (kernel, degree) -> (read bytes, written bytes) per application, cone_256
-    ("pad_volume_kernel", 3): (2.0 * 36897 * 1024, 1.0 * 71874 * 1024),
-    ("pad_volume_yfast_kernel", 3): (2.0 * 65553 * 1024, 1.0 * 72218 * 1024),
-    ("project_kernel", 3): (2.0 * (1295830 + 1045866) * 1024, 1.0 * (147137 + 94671) * 1024),  # two launches
-    ("backproject_cells_kernel", 3): (2.0 * 3007007 * 1024, 1.0 * 5412897 * 1024),
-    ("cells_to_coeffs_kernel", 3): (2.0 * 2481303 * 1024, 1.0 * 65536 * 1024),
-    ("pad_volume_kernel", 0): (2.0 * 36895 * 1024, 1.0 * 67084 * 1024),
-    ("project_kernel", 0): (2.0 * 1069235 * 1024, 1.0 * 254618 * 1024),
-    ("backproject_cells_kernel", 0): (2.0 * 1260068 * 1024, 1.0 * 67106 * 1024),
-    ("cells_to_coeffs_kernel", 0): (2.0 * 32785 * 1024, 1.0 * 65536 * 1024),
+    ("pad_volume_kernel", 3): (2.0 * 36889 * 1024, 1.0 * 71874 * 1024),
+    ("pad_volume_yfast_kernel", 3): (2.0 * 65555 * 1024, 1.0 * 72216 * 1024),
+    ("project_kernel", 3): (2.0 * (1296018 + 1045271) * 1024, 1.0 * (147097 + 94616) * 1024),  # two launches
+    ("backproject_cells_kernel", 3): (2.0 * 3018647 * 1024, 1.0 * 5648772 * 1024),
+    ("cells_to_coeffs_kernel", 3): (2.0 * 2462550 * 1024, 1.0 * 65536 * 1024),
+    ("pad_volume_kernel", 0): (2.0 * 36891 * 1024, 1.0 * 67084 * 1024),
+    ("project_kernel", 0): (2.0 * 1069467 * 1024, 1.0 * 254721 * 1024),
+    ("backproject_cells_kernel", 0): (2.0 * 1254852 * 1024, 1.0 * 67778 * 1024),
+    ("cells_to_coeffs_kernel", 0): (2.0 * 32784 * 1024, 1.0 * 65536 * 1024),
 }
 
 
@@ -91,12 +91,12 @@ TRAFFIC_BYTES = {  # (kernel, degree) -> (read bytes, written bytes) per applica
 L2_FILL_BYTES = {  # (kernel, degree) -> bytes per application, cone_256
     ("pad_volume_kernel", 3): 128.0 * 589824,
     ("pad_volume_yfast_kernel", 3): 128.0 * 1048576,
-    ("project_kernel", 3): 128.0 * (12960493046 + 6705862807),  # two launches
-    ("backproject_cells_kernel", 3): 128.0 * 210638300,
-    ("cells_to_coeffs_kernel", 3): 128.0 * 45215857,
+    ("project_kernel", 3): 128.0 * (12961003828 + 6695955889),  # two launches
+    ("backproject_cells_kernel", 3): 128.0 * 270312933,
+    ("cells_to_coeffs_kernel", 3): 128.0 * 45768280,
     ("pad_volume_kernel", 0): 128.0 * 589824,
-    ("project_kernel", 0): 128.0 * 5704423358,
-    ("backproject_cells_kernel", 0): 128.0 * 194942051,
+    ("project_kernel", 0): 128.0 * 5703665826,
+    ("backproject_cells_kernel", 0): 128.0 * 250924952,
     ("cells_to_coeffs_kernel", 0): 128.0 * 524288,
 }
 PEAK_L2_TBS = 8 * 16 * 128 * 2.4e9 / 1e12

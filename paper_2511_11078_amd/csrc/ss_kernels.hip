@@ -259,20 +259,35 @@ __global__ void __launch_bounds__(256, 4) project_kernel(const float *__restrict
 // forward, each output has a single writer, and the summation order is
 // fixed.
 //
-// Pass 1 blocks own GX x GY x GZ bricks of cells.  Per view a block projects
-// the brick's lattice corners once into LDS (FP32 offsets from the brick
-// centre, every term involving the centre or the source formed in FP64),
-// appends the lines of the brick's pixel rectangle to an LDS table (FP64
-// set-up, anchor re-based at the brick centre), and every thread takes the
-// bounding rectangle of its own cell's eight projected corners as its
-// candidate pixels (about 95 % of them hit the cell).  A thread queues its
-// candidates without reading their lines in a ring, oldest first, and the
-// integration drops the few whose chord through the cell is empty.  The
-// table has two halves filled in turn (up to a few views each):
-// before a half is refilled, each wave runs as many integration rounds as
-// its lane with the most entries in that half needs, and lanes with fewer
-// take entries of the other half in the same rounds, so that the lanes of a
-// wave, whose candidate counts differ view by view, stay busy.
+// Pass 1 blocks own GX x GY x GZ bricks of cells and take the views in
+// batches: as many consecutive views as fit half of the LDS line table (a
+// few hundred lines, up to BATCH_VIEWS views; a view whose shadow is larger
+// than that is taken alone, in segments).  Per batch the block
+//   - fills the half with the lines of each view's pixel rectangle (FP64
+//     set-up, anchor re-based at the brick centre), all threads taking part
+//     whatever the view,
+//   - and every thread computes, view by view, the pixel rectangle of its
+//     own cell's shadow (about 95 % of those lines hit the cell) and appends
+//     it to its queue as one 32-bit run (first table entry, columns, rows).
+// A thread's shadow is bounded around its projected cell centre: with
+// den = 1 at the source plane's parallel through the detector, the position
+// moves by at most F / (den - hn) pixels over the cell, F = half the sum
+// over axes of |du_k - (nu/den) nm_k| taken at the ends of nu/den over the
+// brick, hn half the sum of |nm_k| (0.5 % above the exact bound, no corner
+// table, no LDS reads).  The views' rectangles and per-brick constants are
+// computed by 64 threads for 64 views at a time.  Integration drains the
+// queues: before a half is refilled, each wave runs as many rounds as its
+// lane with the most entries in that half needs, and lanes with fewer take
+// entries of the other half in the same rounds, so that the lanes of a wave,
+// whose candidate counts differ view by view, stay busy.
+//
+// What bounds it: VALU issue, 2.07 hits of about 440 instructions per (cell,
+// view) plus the set-up, at 0.34 wave instructions per SIMD per cycle (degree
+// 3; independent FMAs reach 0.41).  With a corner table, a barrier and a
+// partly filled line set-up per view instead of per batch, and a queue of
+// single entries, cone_256 took 187.5 ms at degree 3 and 70.9 ms at degree 0;
+// with the batches 156 and 50.6 ms (1.43e11 -> 1.32e11 and 3.79e10 -> 2.75e10
+// VALU instructions, half the scalar ones), and bit for bit the same sums.
 //
 // The cell table T holds (n+1)^3 FP32 entries per cell, entry-major
 // (T[a * cells + K], K x-fastest over the cells of a z-chunk), so that both
@@ -281,24 +296,31 @@ __global__ void __launch_bounds__(256, 4) project_kernel(const float *__restrict
 // a chunk of L layers finalises L - n coefficient layers.
 // ---------------------------------------------------------------------------
 constexpr int GX = 8, GY = 8, GZ = 4;
-constexpr int NCORNER = (GX + 1) * (GY + 1) * (GZ + 1);
-constexpr int HITQ_CAP = 32;                    // queued candidates per thread (a ring)
+constexpr int BATCH_VIEWS = 8;        // views per batch: runs per thread and table half
+constexpr int RING = 2 * BATCH_VIEWS; // queued runs per thread
+constexpr int RUN_MAX = 64;           // columns and rows of a batched view's rectangle (6 bits each)
+constexpr int BV_CHUNK = 64;          // views whose brick constants are kept in LDS
+struct BrickViews {
+    float nc[BV_CHUNK], nr[BV_CHUNK], dn[BV_CHUNK];  // centre's numerators and denominator
+    float fc[BV_CHUNK], fr[BV_CHUNK];                // F of the columns and rows
+    int i0[BV_CHUNK], i1[BV_CHUNK], j0[BV_CHUNK], j1[BV_CHUNK];  // the brick's pixel rectangle
+};
 // Line table (two halves) and occupancy per degree: the cubic kernel's
 // registers allow three waves per SIMD, so its table takes what LDS leaves
-// for three blocks per CU beside the candidate queues and two corner tables,
-// counting 160 KiB in 2 KiB units (three blocks of 54,232 bytes did not fit
-// on a CU); lower degrees fit four waves and a smaller table.
+// for three blocks per CU beside the queues, counting 160 KiB in 2 KiB
+// units; lower degrees fit four waves and a smaller table.
 template <int n> struct CellGather {
     static constexpr int waves = n == 3 ? 3 : 4;          // waves per SIMD: blocks per CU
     static constexpr int lds = (160 * 1024 / waves) / 2048 * 2048;
-    static constexpr int fixed = HITQ_CAP * 256 * 2 + 2 * NCORNER * 8 + 16;
-    static constexpr int cap = (lds - fixed) / 40 / 16 * 16;  // lines in the LDS table (40 bytes each)
-    static constexpr int half = cap / 2;
-    static constexpr int views_per_half = n == 3 ? 5 : 3;
-    // wave priority while a block sets up a view (0: the default throughout)
+    static constexpr int fixed = RING * 256 * 4 + (int)sizeof(BrickViews) + 64;
+    static constexpr int half = std::min((lds - fixed) / 40 / 2 / 16 * 16, 480);  // lines per half (40 bytes each)
+    static constexpr int seg_cols = n == 3 ? 376 : 224;  // lines of a segment of a larger view
+    // wave priority while a block sets up a batch (0: the default throughout)
     static constexpr int setup_prio = n == 0 ? 0 : 2;
+    static_assert(2 * half <= 1024, "a run's first entry has 10 bits");
+    static_assert(seg_cols <= half, "a segment fits a half");
 };
-constexpr float PIX_MARGIN = 1.0e-3f;           // pixels; covers FP32 rounding of the corner table
+constexpr float PIX_MARGIN = 1.0e-3f;           // pixels; covers FP32 rounding of the shadow bounds
 
 struct __attribute__((aligned(8))) CellRay {  // 40 bytes
     float a[3];      // point of the line nearest the brick centre, relative to it
@@ -393,7 +415,7 @@ __device__ __forceinline__ void integrate_hit(const CellRay &r, const float lo[3
 
 // Pixels whose centre lies in the continuous detector rectangle
 // [cmin, cmax] x [rmin, rmax] (pixel units), clamped to the detector;
-// PIX_MARGIN absorbs the FP32 rounding of the corner table.
+// PIX_MARGIN absorbs the FP32 rounding of the bounds.
 __device__ __forceinline__ void pixel_rect(float cmin, float cmax, float rmin, float rmax, int R, int C, int &i0,
                                            int &i1, int &j0, int &j1) {
     // clamped in FP32 before converting
@@ -406,24 +428,56 @@ __device__ __forceinline__ void pixel_rect(float cmin, float cmax, float rmin, f
     }
 }
 
-// Bounding rectangle of the projected corners of the lattice box
-// [x0, x0 + sx] x [y0, y0 + sy] x [z0, z0 + sz] (corner table of the brick).
-// The projection of the box is the convex hull of its corners' projections,
-// so every pixel whose line meets the box is in the rectangle.
-__device__ __forceinline__ void corner_bounds(const float2 *corner, int sx, int sy, int sz, int x0, int y0, int z0,
-                                              float &cmin, float &cmax, float &rmin, float &rmax) {
-    cmin = 3.0e38f; cmax = -3.0e38f; rmin = 3.0e38f; rmax = -3.0e38f;
+// One view's constants for the brick centred at `centre`: the numerators and
+// the denominator of the centre's projection (FP64 differences), the brick's
+// pixel rectangle from its eight projected corners, and the shadow
+// half-widths F of its cells.  A corner on or behind the source plane has no
+// bounded shadow: the whole detector, and unbounded F.
+__device__ __forceinline__ void brick_view(const ViewProj &P, const double centre[3], int R, int C, BrickViews &B,
+                                           int s) {
+    const float oc = 0.5f * (float)(C - 1) + P.gac_f, orow = 0.5f * (float)(R - 1) + P.gar_f;
+    const double *c = centre;
+    const float nc = (float)(fma(c[2], P.du_s[2], fma(c[1], P.du_s[1], c[0] * P.du_s[0])) - P.odu);
+    const float nr = (float)(fma(c[2], P.dv_s[2], fma(c[1], P.dv_s[1], c[0] * P.dv_s[0])) - P.odv);
+    const float dn = P.kind == 0 ? 1.0f
+                     : (float)((fma(c[2], P.nrm[2], fma(c[1], P.nrm[1], c[0] * P.nrm[0])) - P.onm) / P.plane);
+    bool bad = false;
+    float gmin = 3.0e38f, gmax = -3.0e38f, hmin = 3.0e38f, hmax = -3.0e38f;
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
-        const int cx = x0 + ((k & 1) ? sx : 0), cy = y0 + ((k & 2) ? sy : 0), cz = z0 + ((k & 4) ? sz : 0);
-        const float2 p = corner[(cz * (GY + 1) + cy) * (GX + 1) + cx];
-        cmin = fminf(cmin, p.x); cmax = fmaxf(cmax, p.x);
-        rmin = fminf(rmin, p.y); rmax = fmaxf(rmax, p.y);
+        const float d[3] = {(k & 1) ? 0.5f * GX : -0.5f * GX, (k & 2) ? 0.5f * GY : -0.5f * GY,
+                            (k & 4) ? 0.5f * GZ : -0.5f * GZ};
+        const float den = fmaf(d[2], P.nmp_f[2], fmaf(d[1], P.nmp_f[1], fmaf(d[0], P.nmp_f[0], dn)));
+        bad = bad || !(den > 0.0f);
+        const float lam = __builtin_amdgcn_rcpf(den);
+        const float g = lam * fmaf(d[2], P.du_f[2], fmaf(d[1], P.du_f[1], fmaf(d[0], P.du_f[0], nc)));
+        const float h = lam * fmaf(d[2], P.dv_f[2], fmaf(d[1], P.dv_f[1], fmaf(d[0], P.dv_f[0], nr)));
+        gmin = fminf(gmin, g); gmax = fmaxf(gmax, g);
+        hmin = fminf(hmin, h); hmax = fmaxf(hmax, h);
     }
+    float fc = 0.0f, fr = 0.0f, gc = 0.0f, gr = 0.0f;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        fc += fabsf(fmaf(-gmin, P.nmp_f[k], P.du_f[k]));
+        gc += fabsf(fmaf(-gmax, P.nmp_f[k], P.du_f[k]));
+        fr += fabsf(fmaf(-hmin, P.nmp_f[k], P.dv_f[k]));
+        gr += fabsf(fmaf(-hmax, P.nmp_f[k], P.dv_f[k]));
+    }
+    int i0 = 0, i1 = C - 1, j0 = 0, j1 = R - 1;
+    if (!bad) pixel_rect(gmin + oc, gmax + oc, hmin + orow, hmax + orow, R, C, i0, i1, j0, j1);
+    B.nc[s] = nc;
+    B.nr[s] = nr;
+    B.dn[s] = dn;
+    B.fc[s] = bad ? 3.0e38f : 0.5f * fmaxf(fc, gc);
+    B.fr[s] = bad ? 3.0e38f : 0.5f * fmaxf(fr, gr);
+    B.i0[s] = i0;
+    B.i1[s] = i1;
+    B.j0[s] = j0;
+    B.j1[s] = j1;
 }
 
 // Three (degree 3, at most 168 VGPRs) or four (lower degrees, 128) waves per
-// SIMD keep as many blocks on a CU, to hide the per-view set-up between
+// SIMD keep as many blocks on a CU, to hide a batch's set-up between its
 // barriers behind other blocks' integration.
 template <int n>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CellGather<n>::waves)))
@@ -433,12 +487,12 @@ backproject_cells_kernel(const float *__restrict__ y, int N0, int N1, int N2, co
     constexpr int NB = n + 1;
     constexpr int qoff = CellBasis<n>::qoff;
     constexpr double kap = (double)Degree<n>::kap;
-    constexpr int CRAY_HALF = CellGather<n>::half, VIEWS_PER_HALF = CellGather<n>::views_per_half;
-    // A view's set-up (corner table, rectangles, line table, queueing) is
-    // short dependent chains ending in a barrier; the integration is long
-    // runs of independent FMAs.  Raising a wave's priority for the set-up
-    // lets each block reach its barrier sooner while the other blocks on the
-    // CU keep the FMA pipes busy (degrees 1-3; the degree-0 kernel, whose
+    constexpr int HALF = CellGather<n>::half, SEG_COLS = CellGather<n>::seg_cols;
+    // A batch's set-up (records, line table, queueing) is short dependent
+    // chains ending in a barrier; the integration is long runs of
+    // independent FMAs.  Raising a wave's priority for the set-up lets each
+    // block reach its barrier sooner while the other blocks on the CU keep
+    // the FMA pipes busy (degrees 1-3; the degree-0 kernel, whose
     // integration is short, runs faster without).
     constexpr int PRIO = CellGather<n>::setup_prio;
     const auto prio_setup = [] {
@@ -448,15 +502,15 @@ backproject_cells_kernel(const float *__restrict__ y, int N0, int N1, int N2, co
         if constexpr (PRIO > 0) __builtin_amdgcn_s_setprio(0);
     };
     static_assert(sizeof(CellRay) == 40, "line record size assumed by the LDS budget");
-    __shared__ CellRay rays[CellGather<n>::cap];
-    __shared__ unsigned short hitq[HITQ_CAP * 256];  // per-thread queue of candidate table indices
-    __shared__ float2 corner[2][NCORNER];            // view v's corner table in [v & 1]
-    __shared__ int badview[2];  // v + 1 in [v & 1] when a corner of view v is on or behind the source plane
+    __shared__ CellRay rays[2 * HALF];
+    __shared__ uint32_t ring[RING * 256];  // per-thread queue of runs
+    __shared__ BrickViews bv;
     const int M0 = N0 + n, M1 = N1 + n;  // cells per row / column
     const int nbx = (M0 + GX - 1) / GX, nby = (M1 + GY - 1) / GY, nbz = (L + GZ - 1) / GZ;
-    const int b = xcd_remap(blockIdx.x, nbx * nby * nbz);
+    const int nbricks = nbx * nby * nbz;
+    const int b = xcd_remap(blockIdx.x, nbricks);
     const int bx = b % nbx, by = (b / nbx) % nby, bz = b / (nbx * nby);
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63;
     const int tx = tid % GX, ty = (tid / GX) % GY, tz = tid / (GX * GY);
     const int c0 = bx * GX + tx, c1 = by * GY + ty, c2 = bz * GZ + tz;  // cell, chunk-relative
     const bool mine = c0 < M0 && c1 < M1 && c2 < L;
@@ -472,170 +526,158 @@ backproject_cells_kernel(const float *__restrict__ y, int N0, int N1, int N2, co
     float acc[NB * NB * NB];
 #pragma unroll
     for (int e = 0; e < NB * NB * NB; ++e) acc[e] = 0.0f;
-    // block-uniform: the half being filled, its entries and views, and
-    // whether the other half has been filled before
-    int half = 0, used = 0, nviews = 0;
-    bool other_filled = false;
-    // this thread's queue: a ring of table indices, oldest first, in slots
-    // qhead + 256 k (mod the ring); the first `nolder` entries belong to the
-    // other half
-    constexpr int QMASK = HITQ_CAP * 256 - 1;
-    int qhead = tid, count = 0, nolder = 0;
 
-    // Detector position (pixel units) of every lattice corner of the brick
-    // for view v, into corner[v & 1]; a corner on or behind the source plane
-    // (no bounded shadow) stores v + 1 into badview[v & 1] (every writer the
-    // same value, so no reset is needed).  View v + 1's table is written
-    // while view v's lines are set up, so that one barrier per view orders
-    // both: each view's phase ends with at least one barrier, table [v & 1]
-    // and flag [v & 1] are read in phase v and rewritten in phase v + 1.
-    auto project_corners = [&](int v) {
-        LocalProj lp;  // the same in every thread
-        make_localproj(vps[v], centre, lp);
-        bool bad = false;
-#pragma unroll
-        for (int it = 0; it < (NCORNER + 255) / 256; ++it) {  // independent iterations
-            const int t = tid + 256 * it;
-            if (t < NCORNER) {
-                const int cx = t % (GX + 1), cy = (t / (GX + 1)) % (GY + 1), cz = t / ((GX + 1) * (GY + 1));
-                const float d[3] = {(float)cx - 0.5f * GX, (float)cy - 0.5f * GY, (float)cz - 0.5f * GZ};
-                float cc = 0.0f, rr = 0.0f;
-                const bool ok = local_to_detector(lp, d, cc, rr);
-                bad = bad || !ok;
-                corner[v & 1][t] = make_float2(cc + oc, rr + orow);
+    // This thread's queue: a ring of runs, oldest first, the next one to
+    // start in slot qhead; the run being consumed is in registers (next
+    // entry, columns and rows left).  `count` entries are left in all, the
+    // oldest `nolder` of them in the half that is not being filled.
+    int qhead = 0, qtail = 0, count = 0, nolder = 0;
+    int ent = 0, cleft = 0, rleft = 0, cols = 0, jump = 0;
+    // integrate up to `rounds` of this thread's oldest entries
+    auto drain = [&](int rounds) {
+        const int npop = min(rounds, count);
+        for (int k = 0; k < npop; ++k) {
+            if (rleft == 0) {  // start the next run
+                const uint32_t d = ring[(qhead & (RING - 1)) * 256 + tid];
+                ++qhead;
+                ent = (int)(d & 1023u);
+                cols = (int)((d >> 10) & 63u) + 1;
+                rleft = (int)((d >> 16) & 63u) + 1;
+                jump = (int)(d >> 22) + 1 - cols;  // from a row's last entry to the next row's first, less 1
+                cleft = cols;
             }
+            const int cur = ent;
+            --cleft;
+            const bool wrap = cleft == 0;
+            ent += wrap ? jump + 1 : 1;
+            cleft = wrap ? cols : cleft;
+            rleft -= wrap ? 1 : 0;
+            integrate_hit<n>(rays[cur], lo, acc);
         }
-        if (bad) badview[v & 1] = v + 1;
+        count -= npop;
+        nolder = max(nolder - npop, 0);
     };
-    if (tid < 2) badview[tid] = -1;
-    __syncthreads();
-    if (V > 0) project_corners(0);
-    __syncthreads();
-
-    for (int v = 0; v < V; ++v) {
-        prio_setup();
-        const float *e = geom + 12 * v;
-        const float2 *cornerv = corner[v & 1];
-        const bool anybad = badview[v & 1] == v + 1;
-        // the brick's pixel rectangle (from its eight corners, the same for
-        // every thread) and this cell's candidate pixels (from its own)
-        int bi0, bi1, bj0, bj1;
-        int mi0 = 0, mi1 = -1, mj0 = 0, mj1 = -1;
-        if (anybad) {
-            bi0 = 0; bi1 = C - 1; bj0 = 0; bj1 = R - 1;
-            if (mine) { mi0 = 0; mi1 = C - 1; mj0 = 0; mj1 = R - 1; }
-        } else {
-            float bc0, bc1, br0, br1;
-            corner_bounds(cornerv, GX, GY, GZ, 0, 0, 0, bc0, bc1, br0, br1);
-            pixel_rect(bc0, bc1, br0, br1, R, C, bi0, bi1, bj0, bj1);
-            if (mine) {
-                float c0, c1, r0, r1;
-                corner_bounds(cornerv, 1, 1, 1, tx, ty, tz, c0, c1, r0, r1);
-                pixel_rect(c0, c1, r0, r1, R, C, mi0, mi1, mj0, mj1);
-            }
-        }
-        if (v + 1 < V) project_corners(v + 1);
-        bool barrier = false;  // block-uniform: a barrier has passed in this view's phase
-        // the view's lines go into the current half of the table in segments
-        // of whole rows (of columns, for a row wider than a half); this cell's
-        // candidates are queued, and integrated before their half is refilled
-        const int W = bi1 - bi0 + 1;
-        if (W > 0 && bj1 >= bj0) {
-            // integer quotients by a float reciprocal: (a + 1/2) / b is at
-            // least 1/(2b) away from an integer, far more than its rounding
-            const int rows_per_seg = max(1, (int)(((float)CRAY_HALF + 0.5f) * __builtin_amdgcn_rcpf((float)W)));
-            const int cols = min(W, CRAY_HALF);
-            for (int cj0 = bj0; cj0 <= bj1; cj0 += rows_per_seg) {
-                const int cj1 = min(bj1, cj0 + rows_per_seg - 1);
-                for (int ci0 = bi0; ci0 <= bi1; ci0 += cols) {
-                    const int ci1 = min(bi1, ci0 + cols - 1);
-                    const int cw = ci1 - ci0 + 1;
-                    const int cn = (cj1 - cj0 + 1) * cw;
-                    if (used + cn > CRAY_HALF || nviews == VIEWS_PER_HALF) {
-                        // switch halves.  Before the other half is refilled,
-                        // every lane retires its entries there; lanes with
-                        // fewer of them integrate entries of this half in the
-                        // same rounds (the wave runs as many rounds as its
-                        // lane with the most entries in the other half)
-                        if (other_filled) {
-                            prio_integrate();
-                            int K = nolder;
+    auto wave_max = [](int x) {
 #pragma unroll
-                            for (int m = 32; m >= 1; m >>= 1) K = max(K, __shfl_xor(K, m));
-                            const int npop = min(K, count);
-                            int idx = hitq[qhead];  // the next entry's index is read a round ahead
-                            for (int k = 0; k < npop; ++k) {
-                                qhead = (qhead + 256) & QMASK;
-                                const int cur = idx;
-                                idx = hitq[qhead];
-                                integrate_hit<n>(rays[cur], lo, acc);
-                            }
-                            count -= npop;
-                            __syncthreads();  // no wave reads the other half any more
-                            prio_setup();
-                        }
-                        nolder = count;  // every queued entry is now in the older half
-                        half ^= 1;
-                        used = 0;
-                        nviews = 0;
-                        other_filled = true;
-                    }
-                    // new entries go past every queued one: no barrier needed
-                    const int tb = half * CRAY_HALF + used;  // first table entry of the segment
-                    const float rcw = __builtin_amdgcn_rcpf((float)cw);
-                    for (int t = tid; t < cn; t += blockDim.x) {
-                        const int q = (int)(((float)t + 0.5f) * rcw);
-                        const int jj = cj0 + q, ii = ci0 + (t - q * cw);
-                        fill_cellray(rays[tb + t], e, kind, R, C, jj, ii, centre,
-                                     y[((int64_t)v * R + jj) * C + ii]);
-                    }
-                    __syncthreads();
-                    barrier = true;
-                    const int j0 = max(mj0, cj0), j1 = min(mj1, cj1);
-                    const int i0 = max(mi0, ci0), i1 = min(mi1, ci1);
-                    const int ni = i1 - i0 + 1, nc = (j1 >= j0 && ni > 0) ? (j1 - j0 + 1) * ni : 0;
-                    if (count + nc <= HITQ_CAP) {
-                        // room for every candidate: one flat loop in the same
-                        // (row, column) order, no overflow test per entry
-                        int e = tb + (j0 - cj0) * cw + (i0 - ci0);  // table entry of the first candidate
-                        int slot = qhead + 256 * count;
-                        for (int k = 0, ii = 0; k < nc; ++k) {
-                            hitq[slot & QMASK] = (unsigned short)e;
-                            slot += 256;
-                            ++ii;
-                            const bool wrap = ii == ni;
-                            e += wrap ? cw - ni + 1 : 1;
-                            ii = wrap ? 0 : ii;
-                        }
-                        count += nc;
-                    } else {
-                        for (int jj = j0; jj <= j1; ++jj)
-                            for (int ii = i0; ii <= i1; ++ii) {
-                                if (count == HITQ_CAP) {  // queue full: integrate its oldest entry now
-                                    integrate_hit<n>(rays[hitq[qhead]], lo, acc);
-                                    qhead = (qhead + 256) & QMASK;
-                                    --count;
-                                    nolder = max(nolder - 1, 0);
-                                }
-                                hitq[(qhead + 256 * count) & QMASK] =
-                                    (unsigned short)(tb + (jj - cj0) * cw + (ii - ci0));
-                                ++count;
-                            }
-                    }
-                    used += cn;
+        for (int m = 32; m >= 1; m >>= 1) x = max(x, __shfl_xor(x, m));
+        return x;
+    };
+
+    // block-uniform: batch number, next view, first column and row of its
+    // next segment (a larger view), views whose records are in LDS
+    int batch = 0, v = 0, si = 0, sj = 0, rec0 = 0, rec1 = 0;
+    while (true) {
+        prio_setup();
+        if (v + BATCH_VIEWS > rec1 && rec1 < V) {
+            // records of the next views (every wave is past its reads of the
+            // old ones: they precede the last barrier)
+            rec0 = v;
+            rec1 = min(v + BV_CHUNK, V);
+            if (tid < rec1 - rec0) brick_view(vps[rec0 + tid], centre, R, C, bv, tid);
+            __syncthreads();
+        }
+        // lane l < BATCH_VIEWS holds view v + l: its pixel rectangle, and the
+        // lines of the views before it
+        const int lv = max(min(v - rec0 + (lane & (BATCH_VIEWS - 1)), rec1 - rec0 - 1), 0);
+        int vi0 = bv.i0[lv], vj0 = bv.j0[lv];
+        int W = bv.i1[lv] - vi0 + 1, H = bv.j1[lv] - vj0 + 1;
+        const bool over = W > RUN_MAX || H > RUN_MAX || W * H > HALF;
+        const int own = over ? HALF + 1 : W * H;  // 0 for a view that misses the detector
+        int upto = own;                           // inclusive sum over lanes 0 .. l
+#pragma unroll
+        for (int m = 1; m < BATCH_VIEWS; m <<= 1) {
+            const int t = __shfl_up(upto, m, BATCH_VIEWS);
+            upto += (lane & (BATCH_VIEWS - 1)) >= m ? t : 0;
+        }
+        const bool fits = lane < BATCH_VIEWS && v + lane < V && upto <= HALF;
+        int K = __popcll(__ballot(fits));  // views in this batch (the sums do not decrease)
+        // a view too large for a batch comes alone, in segments of whole rows
+        // (of columns, for a row wider than SEG_COLS)
+        const bool done = v >= V, large = K == 0;
+        // every wave retires its entries of the half that is refilled; before
+        // a segment and at the end, all of them
+        prio_integrate();
+        drain(large ? INT32_MAX : wave_max(nolder));
+        if (done) break;
+        if (batch >= 2) __syncthreads();
+        prio_setup();
+        const int half = (batch & 1) * HALF;
+        ++batch;
+        nolder = count;  // every queued entry is now in the older half
+        int tb = upto - own, lines;
+        const int vb = v;
+        if (large) {
+            const int BW = __builtin_amdgcn_readlane(W, 0), BH = __builtin_amdgcn_readlane(H, 0);
+            const int scols = min(BW, SEG_COLS), srows = SEG_COLS / scols;
+            vi0 += si;
+            vj0 += sj;
+            W = min(scols, BW - si);
+            H = min(srows, BH - sj);
+            tb = 0;
+            lines = W * H;
+            K = 1;
+            si += scols;
+            if (si >= BW) {
+                si = 0;
+                sj += srows;
+                if (sj >= BH) {
+                    sj = 0;
+                    ++v;
                 }
             }
-            ++nviews;
+        } else {
+            lines = __builtin_amdgcn_readlane(upto, K - 1);
+            v += K;
         }
-        if (!barrier) __syncthreads();
-    }
-    prio_integrate();
-    int idx = hitq[qhead];
-    for (int k = 0; k < count; ++k) {
-        qhead = (qhead + 256) & QMASK;
-        const int cur = idx;
-        idx = hitq[qhead];
-        integrate_hit<n>(rays[cur], lo, acc);
+        for (int base = 0; base < lines; base += 256) {
+            const int t = base + tid;
+            int idx = 0;  // the view of line t
+            for (int k = 1; k < K; ++k) idx += t >= __builtin_amdgcn_readlane(tb, k) ? 1 : 0;
+            const int w = __shfl(W, idx), ti = __shfl(vi0, idx), tj = __shfl(vj0, idx), tt = t - __shfl(tb, idx);
+            if (t < lines) {
+                // integer quotient by a float reciprocal: (a + 1/2) / b is at
+                // least 1/(2b) away from an integer, far more than its rounding
+                const int q = (int)(((float)tt + 0.5f) * __builtin_amdgcn_rcpf((float)w));
+                const int jj = tj + q, ii = ti + (tt - q * w), vv = vb + idx;
+                fill_cellray(rays[half + t], geom + 12 * vv, kind, R, C, jj, ii, centre,
+                             y[((int64_t)vv * R + jj) * C + ii]);
+            }
+        }
+        for (int k = 0; k < K; ++k) {
+            const int w = __builtin_amdgcn_readlane(W, k), h = __builtin_amdgcn_readlane(H, k);
+            if (w <= 0 || h <= 0) continue;
+            const ViewProj &P = vps[vb + k];
+            const int s = vb + k - rec0;
+            const float d0 = lo[0] + 0.5f, d1 = lo[1] + 0.5f, d2 = lo[2] + 0.5f;
+            const float nu = fmaf(d2, P.du_f[2], fmaf(d1, P.du_f[1], fmaf(d0, P.du_f[0], bv.nc[s])));
+            const float nv = fmaf(d2, P.dv_f[2], fmaf(d1, P.dv_f[1], fmaf(d0, P.dv_f[0], bv.nr[s])));
+            const float den = fmaf(d2, P.nmp_f[2], fmaf(d1, P.nmp_f[1], fmaf(d0, P.nmp_f[0], bv.dn[s])));
+            const float lam = __builtin_amdgcn_rcpf(den), rr = __builtin_amdgcn_rcpf(den - P.hn_f);
+            const bool open = !(den > P.hn_f);  // a corner on or behind the source plane: no bounded shadow
+            // relative to the rectangle's first pixel
+            const float cc = fmaf(lam, nu, P.gac_f + (oc - (float)__builtin_amdgcn_readlane(vi0, k)));
+            const float cr = fmaf(lam, nv, P.gar_f + (orow - (float)__builtin_amdgcn_readlane(vj0, k)));
+            const float ec = fmaf(bv.fc[s], rr, PIX_MARGIN), er = fmaf(bv.fr[s], rr, PIX_MARGIN);
+            const float wf = (float)(w - 1), hf = (float)(h - 1);
+            const float fi0 = open ? 0.0f : fmaxf(ceilf(cc - ec), 0.0f), fi1 = open ? wf : fminf(floorf(cc + ec), wf);
+            const float fj0 = open ? 0.0f : fmaxf(ceilf(cr - er), 0.0f), fj1 = open ? hf : fminf(floorf(cr + er), hf);
+            if (mine && fi0 <= fi1 && fj0 <= fj1) {
+                const int ni = (int)(fi1 - fi0), nj = (int)(fj1 - fj0);  // columns and rows, less 1
+                const int first = half + __builtin_amdgcn_readlane(tb, k) + (int)fmaf(fj0, (float)w, fi0);
+                if (large) {  // the queue is empty: straight to the registers
+                    ent = first;
+                    cols = cleft = ni + 1;
+                    rleft = nj + 1;
+                    jump = w - cols;
+                } else {
+                    ring[(qtail & (RING - 1)) * 256 + tid] =
+                        (uint32_t)first | (uint32_t)ni << 10 | (uint32_t)nj << 16 | (uint32_t)(w - 1) << 22;
+                    ++qtail;
+                }
+                count += (ni + 1) * (nj + 1);
+            }
+        }
+        __syncthreads();  // the half is filled; every record of this batch has been read
     }
     // moments -> per-basis integrals: apply the blending map along each axis
     if constexpr (n > 0) {

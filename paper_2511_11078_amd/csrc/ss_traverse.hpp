@@ -60,6 +60,11 @@ struct ViewProj {    // detector coordinates of a world point (FP64 set-up)
     float du_f[3], dv_f[3], nm_f[3];
     float ac_f, ar_f, plane_f;  // (s - d0) . du_s, (s - d0) . dv_s, plane
     int kind;
+    // for the knot-cell gather, where both kinds read col = ac + nu / den,
+    // row = ar + nv / den: nrm / plane (0 for parallel beams, whose den is 1),
+    // half the sum of its magnitudes, and the two additive terms (0 for
+    // parallel beams)
+    float nmp_f[3], hn_f, gac_f, gar_f;
 };
 
 // Continuous pixel coordinates (column, row) of world point X.
@@ -128,6 +133,16 @@ __host__ __device__ inline void make_viewproj(const float *__restrict__ e, int k
     P.ac_f = (float)(sd[0] * P.du_s[0] + sd[1] * P.du_s[1] + sd[2] * P.du_s[2]);
     P.ar_f = (float)(sd[0] * P.dv_s[0] + sd[1] * P.dv_s[1] + sd[2] * P.dv_s[2]);
     P.plane_f = (float)P.plane;
+    const double ip = kind == 0 || P.plane == 0.0 ? 0.0 : 1.0 / P.plane;
+    double hn = 0.0;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        P.nmp_f[k] = (float)(P.nrm[k] * ip);
+        hn += 0.5 * (P.nrm[k] * ip < 0.0 ? -P.nrm[k] * ip : P.nrm[k] * ip);
+    }
+    P.hn_f = (float)hn;
+    P.gac_f = kind == 0 ? 0.0f : P.ac_f;
+    P.gar_f = kind == 0 ? 0.0f : P.ar_f;
 }
 
 // Detector coordinates of points X = c + delta near a centre c, evaluated in

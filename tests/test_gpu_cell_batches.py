@@ -1,0 +1,61 @@
+"""View batches of the quadrature adjoint's cell gather against the FP64 oracle.
+
+A block takes its views in batches: up to 8 consecutive views whose line
+rectangles together fit half of its line table, a larger view alone in
+segments, per-view constants for 64 views at a time.  The cases sit on the
+edges of those rules; the bar is the quadrature form's (relative L2 1e-5 for
+FP32 arithmetic, 1e-4 for degree 0, whose outputs jump where a line runs
+within rounding of a voxel face).
+"""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2511_11078_amd import synth
+from paper_2511_11078_amd.ops import Context
+
+from gpu_helpers import rel_l2, say, to_gpu, to_np
+
+pytestmark = pytest.mark.gpu
+
+
+def _tilted(views, pitches, shift, seed):
+    """Parallel views with a pitch of their own each; every third one's
+    detector moved by `shift` pixels along its columns."""
+    vecs = []
+    for k, w in enumerate(synth.uniform_directions(views, seed=seed)):
+        u, v = synth.detector_frame(w)
+        p = pitches[k % len(pitches)]
+        vecs.append(np.concatenate([w, (shift * p if k % 3 == 0 else 0.0) * u, p * u, p * v]))
+    return np.asarray(vecs, dtype=np.float32)
+
+
+CASES = {
+    # name: (views, rows, cols, pitches, detector shift)
+    "one_view": (1, 9, 11, [1.0], 0.0),
+    "seven_views_one_pixel": (7, 1, 1, [1.0], 0.0),
+    "records_of_65_views": (65, 6, 7, [1.0], 0.0),
+    "records_of_129_views_some_missing": (129, 5, 6, [1.1], 40.0),
+    # 8 x 8 x 4 cells span about 12 x 12 pixels at pitch 1: from batches of
+    # several views, over one view per batch, to views in segments, in turn
+    "batches_and_segments_in_turn": (22, 60, 90, [1.0, 0.62, 0.5, 0.2], 0.0),
+    "wider_than_a_run": (5, 4, 300, [0.11], 0.0),
+}
+
+
+@pytest.mark.parametrize("n", [0, 1, 2, 3])
+@pytest.mark.parametrize("case", list(CASES))
+def test_view_batches(n, case):
+    say(f"cell gather {case} n={n}")
+    views, R, C, pitches, shift = CASES[case]
+    dims = (11, 9, 6)
+    geom = synth.Geometry("parallel", views, R, C, _tilted(views, pitches, shift, seed=300 + n))
+    y = np.random.default_rng(310 + n).standard_normal((views, R, C)).astype(np.float32)
+    ctx = Context(n, "quad", 0)
+    got = to_np(ctx.backproject(to_gpu(y), geom, dims))
+    ctx.close()
+    want = oracle.backproject_subset(y, geom, dims, n)
+    e = rel_l2(got, want)
+    say(f"  rel-L2 {e:.3e}")
+    assert np.abs(want).max() > 0
+    assert e <= (1e-5 if n > 0 else 1e-4)
