@@ -61,25 +61,25 @@ MLP_FLOPS_PER_PAIR = 2.0 * 3 * 64 * 64 + 2.0 * 5 * 64 + 2.0 * 64   # hidden BF16
 MLP_TRANS_PER_PAIR = 2 * 4 * 64   # SiLU of 4 x 64 hidden units: one exp and one reciprocal each
 
 
-# HBM bytes per application (forward or adjoint: the launches of each kernel
-# summed; the cubic forward launches project_kernel twice, once per copy of
-# the coefficients) of the quadrature kernels on cone_256, from rocprofv3
+# HBM bytes per application (forward or adjoint) of the quadrature kernels on cone_256, from rocprofv3
 # FETCH_SIZE and WRITE_SIZE (KiB per dispatch) scaled by what the same
 # counters read for a plain 256 MiB device copy (x2.000 and x1.000); see
 # profiles/cone256_traffic_counters.md.  Valid only for the kernel sources they
 # were measured on (SHA-256 over QUAD_SOURCES); otherwise reported as null.
 QUAD_SOURCES = ["csrc/ss_kernels.hip", "csrc/ss_math.hpp", "csrc/ss_traverse.hpp", "csrc/ss_kernels.hpp"]
-TRAFFIC_SHA256 = "88892611331cb2c1d1e55582ebdeccd00b5bb9e30f02497ee01b64cbb2884731"
+TRAFFIC_SHA256 = "c580b437c23a8cebabf35f2db8d6132e404372d2385cfd0ecd7ec973b326af94"
 TRAFFIC_BYTES = {  # (kernel, degree) -> (read bytes, written bytes) per application, cone_256
-    ("pad_volume_kernel", 3): (2.0 * 36889 * 1024, 1.0 * 71874 * 1024),
-    ("pad_volume_yfast_kernel", 3): (2.0 * 65555 * 1024, 1.0 * 72216 * 1024),
-    ("project_kernel", 3): (2.0 * (1296018 + 1045271) * 1024, 1.0 * (147097 + 94616) * 1024),  # two launches
-    ("backproject_cells_kernel", 3): (2.0 * 3018647 * 1024, 1.0 * 5648772 * 1024),
-    ("cells_to_coeffs_kernel", 3): (2.0 * 2462550 * 1024, 1.0 * 65536 * 1024),
-    ("pad_volume_kernel", 0): (2.0 * 36891 * 1024, 1.0 * 67084 * 1024),
-    ("project_kernel", 0): (2.0 * 1069467 * 1024, 1.0 * 254721 * 1024),
-    ("backproject_cells_kernel", 0): (2.0 * 1254852 * 1024, 1.0 * 67778 * 1024),
-    ("cells_to_coeffs_kernel", 0): (2.0 * 32784 * 1024, 1.0 * 65536 * 1024),
+    ("pad_volume_kernel", 3): (2.0 * 36888 * 1024, 1.0 * 71874 * 1024),
+    ("pad_volume_zfast_kernel", 3): (2.0 * 65559 * 1024, 1.0 * 72259 * 1024),
+    ("pad_volume_yfast_kernel", 3): (0.0, 0.0),  # a y-fastest copy is no longer made
+    ("project_kernel", 3): (2.0 * 3801477 * 1024, 1.0 * 255451 * 1024),
+    ("backproject_cells_kernel", 3): (2.0 * 3018571 * 1024, 1.0 * 5654054 * 1024),
+    ("cells_to_coeffs_kernel", 3): (2.0 * 2469840 * 1024, 1.0 * 65536 * 1024),
+    ("pad_volume_zfast_kernel", 0): (2.0 * 65561 * 1024, 1.0 * 80221 * 1024),
+    ("pad_volume_kernel", 0): (2.0 * 36888 * 1024, 1.0 * 67084 * 1024),
+    ("project_kernel", 0): (2.0 * 2964952 * 1024, 1.0 * 268032 * 1024),
+    ("backproject_cells_kernel", 0): (2.0 * 1251143 * 1024, 1.0 * 67642 * 1024),
+    ("cells_to_coeffs_kernel", 0): (2.0 * 32783 * 1024, 1.0 * 65536 * 1024),
 }
 
 
@@ -90,13 +90,15 @@ TRAFFIC_BYTES = {  # (kernel, degree) -> (read bytes, written bytes) per applica
 # at 2.4 GHz; the best L2-read rate measured by peaks_probe.hip is below it.
 L2_FILL_BYTES = {  # (kernel, degree) -> bytes per application, cone_256
     ("pad_volume_kernel", 3): 128.0 * 589824,
-    ("pad_volume_yfast_kernel", 3): 128.0 * 1048576,
-    ("project_kernel", 3): 128.0 * (12961003828 + 6695955889),  # two launches
-    ("backproject_cells_kernel", 3): 128.0 * 270312933,
-    ("cells_to_coeffs_kernel", 3): 128.0 * 45768280,
+    ("pad_volume_zfast_kernel", 3): 128.0 * 1048576,
+    ("pad_volume_yfast_kernel", 3): 0.0,
+    ("project_kernel", 3): 128.0 * 10405670636,
+    ("backproject_cells_kernel", 3): 128.0 * 270323721,
+    ("cells_to_coeffs_kernel", 3): 128.0 * 45318638,
+    ("pad_volume_zfast_kernel", 0): 128.0 * 1048576,
     ("pad_volume_kernel", 0): 128.0 * 589824,
-    ("project_kernel", 0): 128.0 * 5703665826,
-    ("backproject_cells_kernel", 0): 128.0 * 250924952,
+    ("project_kernel", 0): 128.0 * 2107709345,
+    ("backproject_cells_kernel", 0): 128.0 * 250920976,
     ("cells_to_coeffs_kernel", 0): 128.0 * 524288,
 }
 PEAK_L2_TBS = 8 * 16 * 128 * 2.4e9 / 1e12
@@ -380,11 +382,10 @@ def main():
                 fl_f = R * cells_per_ray * fwd_unit_flops(n)
                 fl_a = (R * cells_per_ray * adj_unit_flops(n) + ncells * adj_cell_flops(n)
                         + nb3 * float(np.prod(dims)))
-                # degree 3 walks each view in one of two copies of the
-                # coefficients (x or y fastest): two pads, two launches
-                fwd_name = (f"pad_volume_kernel + pad_volume_yfast_kernel + project_kernel<{n}> "
-                            f"(knot-cell walk, two launches)" if n == 3 else
-                            f"pad_volume_kernel + project_kernel<{n}> (knot-cell walk)")
+                # each view is walked in one of two copies of the
+                # coefficients (z or x fastest): two pads, one launch
+                fwd_name = (f"pad_volume_zfast_kernel + pad_volume_kernel + project_kernel<{n}> "
+                            f"(knot-cell walk)")
                 for name, ms, fl, unit in (
                         (fwd_name, fwd_ms, fl_f,
                          f"{fwd_unit_flops(n):.0f} flop per (line, cell) x {cells_per_ray:.1f} cells/line"),

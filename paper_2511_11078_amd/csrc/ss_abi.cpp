@@ -311,7 +311,12 @@ static ss_status run_transform(ss_ctx *ctx, bool forward, const float *in, const
         a.coeffs = in;
         a.sino = out;
         if (ctx->form == SS_FORM_QUAD_FP32) {
-            if (ss_status s = ensure_cells(ctx, ss::project_quad_scratch_floats(ctx->degree, a.N))) return s;
+            const int64_t one = ss::project_quad_scratch_floats(ctx->degree, a.N);
+            const int64_t all = one * ss::project_quad_copies(ctx->degree, a.N);
+            if (all > ctx->cell_limit || ensure_cells(ctx, all) != SS_OK) {
+                (void)hipGetLastError();  // of a second copy that does not fit
+                if (ss_status s = ensure_cells(ctx, one)) return s;
+            }
             a.scratch = ctx->d_cells;
             a.scratch_floats = ctx->cells_cap;
         }

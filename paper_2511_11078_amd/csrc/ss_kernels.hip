@@ -13,6 +13,7 @@
 
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 
 namespace ss {
 
@@ -33,53 +34,66 @@ __global__ void __launch_bounds__(256) pad_volume_kernel(const float *__restrict
     }
 }
 
-// The same copy with x and y exchanged (y fastest: element (x, y, z) at
-// ((z + P) (N0 + 2P) + x + P) (N1 + 2P) + y + P), for the views the forward
-// walks in that order; each block transposes a 32 x 32 (x, y) tile of one
-// z layer through LDS.
+// The same copy with z fastest (element (x, y, z) at
+// ((y + P) (N0 + 2P) + x + P) (N2 + 2P) + z + P); each block transposes a
+// 32 x 32 (x, z) tile of one y layer through LDS.
 constexpr int PAD_T = 32;
-__global__ void __launch_bounds__(256) pad_volume_yfast_kernel(const float *__restrict__ c, int N0, int N1, int N2,
-                                                               int P, float *__restrict__ out) {
-    __shared__ float tile[PAD_T][PAD_T + 1];  // [y][x] of the tile
-    const int Sx = N0 + 2 * P, Sy = N1 + 2 * P;
-    const int tiles_x = (Sx + PAD_T - 1) / PAD_T, tiles_y = (Sy + PAD_T - 1) / PAD_T;
-    const int bx = blockIdx.x % tiles_x, by = (blockIdx.x / tiles_x) % tiles_y;
-    const int zp = blockIdx.x / (tiles_x * tiles_y);  // padded z layer
-    const int z = zp - P;
-    const int tx = threadIdx.x % PAD_T, ty = threadIdx.x / PAD_T;  // 32 x 8
-#pragma unroll
-    for (int k = 0; k < PAD_T; k += 8) {
-        const int x = bx * PAD_T + tx - P, yy = by * PAD_T + ty + k - P;
-        const bool in = x >= 0 && x < N0 && yy >= 0 && yy < N1 && z >= 0 && z < N2;
-        tile[ty + k][tx] = in ? c[((int64_t)z * N1 + yy) * N0 + x] : 0.0f;
+__global__ void __launch_bounds__(256) pad_volume_zfast_kernel(const float *__restrict__ c, int N0, int N1, int N2,
+                                                              int P, float *__restrict__ out) {
+    __shared__ float tile[PAD_T][PAD_T + 1];
+    const int Sx = N0 + 2 * P, Sz = N2 + 2 * P;
+    const int nx = (Sx + PAD_T - 1) / PAD_T, nz = (Sz + PAD_T - 1) / PAD_T;
+    const int yp = (int)(blockIdx.x / (nx * nz)), b = (int)(blockIdx.x % (nx * nz)), bz = b / nx, bx = b % nx;
+    const int tx = threadIdx.x % PAD_T, ty = threadIdx.x / PAD_T;
+    const int y = yp - P;
+    for (int k = 0; k < PAD_T; k += 256 / PAD_T) {
+        const int xp = bx * PAD_T + tx, zp = bz * PAD_T + ty + k, x = xp - P, z = zp - P;
+        const bool in = x >= 0 && x < N0 && y >= 0 && y < N1 && z >= 0 && z < N2;
+        tile[ty + k][tx] = in ? c[((int64_t)z * N1 + y) * N0 + x] : 0.0f;
     }
     __syncthreads();
-#pragma unroll
-    for (int k = 0; k < PAD_T; k += 8) {
-        const int xp = bx * PAD_T + ty + k, yp = by * PAD_T + tx;
-        if (xp < Sx && yp < Sy) out[((int64_t)zp * Sx + xp) * Sy + yp] = tile[tx][ty + k];
+    for (int k = 0; k < PAD_T; k += 256 / PAD_T) {
+        const int zp = bz * PAD_T + tx, xp = bx * PAD_T + ty + k;
+        if (xp < Sx && zp < Sz) out[((int64_t)yp * Sx + xp) * Sz + zp] = tile[tx][ty + k];
     }
 }
 
-// Whether the forward (degrees 1 to 3) walks view e in the y-fastest copy.
-// Measured per 5-degree range of circular cone trajectories (256^3 and
-// 512^3, degree 3; degrees 2 and 1 gain as much from it): with
-// phi the angle between the view's central ray and its dominant horizontal
-// axis, rows along the minor horizontal axis are faster for phi < 15
-// degrees and rows along the dominant axis for 15 <= phi < 35; beyond, and
-// for views whose central ray is mostly along z, the x-fastest copy.  Both
-// copies hold the same values, so the choice changes only the FP32
-// rounding order of the contraction, not what is computed.
-__device__ __forceinline__ bool view_walks_yfast(const float *__restrict__ e, int kind) {
+// How the forward walks view e.
+//
+// What limits the walk beside its arithmetic is the rate of the L1 cache's
+// row reads: a 16-byte read per lane costs, for each group of four lanes, one
+// step per cache-line segment the four touch (loads alone, the integral
+// replaced by a sum, took 146 of cone_256's 164 ms with rows along x or y,
+// whatever the occupancy).  So the lanes of a wave are laid along the
+// detector direction that runs best along an axis, over the copy with that
+// axis fastest: z (the rows of a circular trajectory: cone_256 degree 3
+// 163.5 -> 150 ms, degree 2 85.5 -> 72, degree 1 38.5 -> 29, degree 0
+// 23.5 -> 12 ms), or x where that fits better (rays along z).
+//
+// `yorder`: which of x and y is contracted first (y: central ray within 15
+// degrees of x, or between 15 and 35 degrees of y).  It has no bearing on
+// speed; it fixes the order of the FP32 sums.
+struct ViewWalk {
+    bool yorder, xcopy, rows;  // rows: lanes along the detector's rows
+};
+template <int n>
+__device__ __forceinline__ ViewWalk view_walk(const float *__restrict__ e, int kind) {
+    ViewWalk vw;
     float d[3];
 #pragma unroll
     for (int k = 0; k < 3; ++k) d[k] = kind != 0 ? e[3 + k] - e[k] : e[k];  // cone: source -> detector centre
     const float ax = fabsf(d[0]), ay = fabsf(d[1]), az = fabsf(d[2]);
     const float hi = fmaxf(ax, ay), lo = fminf(ax, ay);
-    if (!(az < hi)) return false;
     const float s = lo / hi;                        // tan(phi)
     constexpr float T15 = 0.26794919f, T35 = 0.70020754f;
-    return ax >= ay ? s < T15 : (s >= T15 && s < T35);
+    vw.yorder = n >= 1 && az < hi && (ax >= ay ? s < T15 : (s >= T15 && s < T35));
+    // squared cosines of the detector's two directions with z and x
+    const float iu = 1.0f / (e[6] * e[6] + e[7] * e[7] + e[8] * e[8]);
+    const float iv = 1.0f / (e[9] * e[9] + e[10] * e[10] + e[11] * e[11]);
+    const float zu = e[8] * e[8] * iu, zv = e[11] * e[11] * iv, xu = e[6] * e[6] * iu, xv = e[9] * e[9] * iv;
+    vw.xcopy = !vw.yorder && fmaxf(xu, xv) > fmaxf(zu, zv);
+    vw.rows = vw.xcopy ? xv > xu : !(zu > zv);
+    return vw;
 }
 
 // ---------------------------------------------------------------------------
@@ -93,32 +107,129 @@ __device__ __forceinline__ bool view_walks_yfast(const float *__restrict__ e, in
 // same Gauss-Legendre terms as the slab-by-slab per-basis sum, evaluated
 // with the node positions and per-axis weights shared by the (n+1)^3 bases.
 // ---------------------------------------------------------------------------
-// Launched once per copy: with yfast = 0 on the x-fastest copy for the views
-// that walk it, with yfast = 1 on the y-fastest copy for the others (blocks
-// of the other views return at once); the walk then runs with x and y
-// exchanged.
+
+// Launches of up to this many 16 x 16-pixel tiles share each line among four
+// lanes (project_kernel).
+constexpr int64_t FWD_SHARED_TILES = 2048;
+// Largest padded copy (floats, 1 GiB) that is kept in both orders, so that
+// one launch walks every view.
+constexpr int64_t FWD_BOTH_FLOATS = (int64_t)1 << 28;
+
+// pointers that keep their address space through an empty asm
+typedef const __attribute__((address_space(1))) char *GlobalBytes;
+typedef const __attribute__((address_space(1))) float *GlobalFloats;
+
+// v_min_f64 as it stands: fmin() quiets both operands first, two more FP64
+// instructions each (no NaN reaches the walk)
+__device__ __forceinline__ double min64(double a, double b) {
+    double r;
+    asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+
+// One (line, cell) unit: half the integral of c's restriction to the cell
+// over xi in [-1, 1], from the cell's coefficient block.  lc: local
+// coordinates of the chord's mid-point, dl: their step to its end.
 template <int n>
-__global__ void __launch_bounds__(256, 4) project_kernel(const float *__restrict__ cp, int N0, int N1, int N2,
-                                                      const float *__restrict__ geom, int kind, int V, int R,
-                                                      int C, float *__restrict__ y, int yfast) {
+__device__ __forceinline__ float cell_integral(const float (&cb)[n + 1][n + 1][n + 1], const float lc[3],
+                                               const float dl[3]) {
     using Rule = GLRule<Degree<n>::m>;
+    constexpr int NB = n + 1;
+    float seg = 0.0f;
+#pragma unroll
+    for (int l = 0; l < Rule::m; ++l) {
+        const float xi = Rule::x(l);
+        float w1[NB], w2[NB], w3[NB];
+        cell_weights<n>(xi == 0.0f ? lc[0] : fmaf(dl[0], xi, lc[0]), w1);
+        cell_weights<n>(xi == 0.0f ? lc[1] : fmaf(dl[1], xi, lc[1]), w2);
+        cell_weights<n>(xi == 0.0f ? lc[2] : fmaf(dl[2], xi, lc[2]), w3);
+        float f = 0.0f;
+#pragma unroll
+        for (int a3 = 0; a3 < NB; ++a3) {
+            float g = 0.0f;
+#pragma unroll
+            for (int a2 = 0; a2 < NB; ++a2) {
+                float r = 0.0f;
+#pragma unroll
+                for (int a1 = 0; a1 < NB; ++a1) r = fmaf(w1[a1], cb[a3][a2][a1], r);
+                g = fmaf(w2[a2], r, g);
+            }
+            f = fmaf(w3[a3], g, f);
+        }
+        seg = fmaf(0.5f * Rule::w(l), f, seg);
+    }
+    return seg;
+}
+
+// value of lane (quad base + P) of each quad
+template <int P>
+__device__ __forceinline__ float quad_lane(float v) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), P * 0x55, 0xf, 0xf, true));
+}
+
+// `which` = 2: every view, each in the copy it walks (view_walk; both copies
+// are there).  0 and 1: only the views of the z- and of the x-fastest copy
+// (blocks of the others return at once), for a scratch that holds one copy
+// at a time.
+//
+// What bounds it at degree 3: VALU issue (the cell integral's about 630
+// instructions; with every load at one address the kernel took 137 ms on
+// cone_256) and the L1 reads (view_walk).  The walk around the integral is
+// kept short: cell indices are carried as the FP64 numbers and the byte
+// offset the cell needs, an axis that reaches its plane advances under its
+// own mask (ties advance together instead of by cells of no length), and a
+// row's address is a scalar base plus that one 32-bit offset (WIDE: copies
+// above 4 GiB, 64-bit).  727 -> 640 VALU instructions per (line, cell).
+//
+// LPL lanes share a line: LPL = 4 lets a launch of few lines fill the chip
+// (small_parallel_32: 450 -> 115 us for 288 tiles).  Each of the four walks
+// all of the line's cells, integrates every fourth one, and all four add the
+// terms in the line's order, so that the sum is the same bit for bit.
+template <int n, int LPL, bool WIDE>
+__global__ void __launch_bounds__(256, n == 3 ? 3 : 4) project_kernel(const float *__restrict__ cz,
+                                                                     const float *__restrict__ cx, int N0, int N1,
+                                                                     int N2, const float *__restrict__ geom, int kind,
+                                                                     int V, int R, int C, float *__restrict__ y,
+                                                                     int which) {
     constexpr int NB = n + 1;
     constexpr double h = (double)Degree<n>::h;
     constexpr double kap = (double)Degree<n>::kap;
     constexpr int qoff = CellBasis<n>::qoff;
+    using Off = typename std::conditional<WIDE, uint64_t, uint32_t>::type;
     const int tR = (R + 15) / 16, tC = (C + 15) / 16;
-    int v, tr, tc;
-    if (!fwd_block_tile(V, tR, tC, v, tr, tc)) return;  // padding slot
-    if (v < V && (n >= 1 && view_walks_yfast(geom + 12 * v, kind)) != (yfast != 0)) return;  // the other copy's view
+    int v, tr, tc_, part = 0;
+    if constexpr (LPL == 1) {
+        if (!fwd_block_tile(V, tR, tC, v, tr, tc_)) return;  // padding slot
+    } else {
+        // four blocks per 16 x 16-pixel tile, tiles innermost: a launch this
+        // small spreads evenly, and its volume stays in every L2
+        const int t = blockIdx.x / LPL;
+        part = blockIdx.x % LPL;
+        tc_ = t % tC;
+        tr = (t / tC) % tR;
+        v = t / (tC * tR);
+    }
+    if (v >= V) return;
+    const ViewWalk vw = view_walk<n>(geom + 12 * v, kind);
+    if (which != 2 && vw.xcopy != (which != 0)) return;  // the other copy's view
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int j = tr * 16 + (wave >> 1) * 8 + (lane >> 3);
-    const int i = tc * 16 + (wave & 1) * 8 + (lane & 7);
-    if (v >= V || j >= R || i >= C) return;
-    // the walk runs in the copy's axis order: (x, y, z), or (y, x, z)
-    const int N[3] = {yfast ? N1 : N0, yfast ? N0 : N1, N2};
+    const int sub = lane & (LPL - 1);
+    int j, i;
+    if constexpr (LPL == 1) {
+        // a wave takes 16 x 4 pixels, consecutive lanes along the long side
+        const int along = lane & 15, across = wave * 4 + (lane >> 4);
+        j = tr * 16 + (vw.rows ? along : across);
+        i = tc_ * 16 + (vw.rows ? across : along);
+    } else {
+        j = tr * 16 + (part >> 1) * 8 + (wave >> 1) * 4 + (lane >> 4);
+        i = tc_ * 16 + (part & 1) * 8 + (wave & 1) * 4 + ((lane >> 2) & 3);
+    }
+    if (j >= R || i >= C) return;
+    // the walk runs in the order of the contractions: (x, y, z), or (y, x, z)
+    const int N[3] = {vw.yorder ? N1 : N0, vw.yorder ? N0 : N1, N2};
     const double centre[3] = {0.0, 0.0, 0.0};
     LineD L = make_line(geom + 12 * v, kind, R, C, j, i, centre);
-    if (yfast) {
+    if (vw.yorder) {
         const double a0 = L.a[0], w0 = L.w[0];
         L.a[0] = L.a[1]; L.a[1] = a0;
         L.w[0] = L.w[1]; L.w[1] = w0;
@@ -144,102 +255,154 @@ __global__ void __launch_bounds__(256, 4) project_kernel(const float *__restrict
             }
         }
         if (hit && t0 < t1) {
-            // DDA state per axis
-            int m[3], stp[3];
-            double tmax[3], tdel[3];
-            // a point just past the entry (the entry lies on a knot plane)
-            const double tm0 = t0 + fmin(1e-6, 0.5 * (t1 - t0));
+            // zero-padded copy of the coefficients (FWD_PAD(n) layers per
+            // side), and its strides in bytes along the walk's axes
+            constexpr int P = FWD_PAD(n);
+            const int64_t Sx = N0 + 2 * P, Sy = N1 + 2 * P, Sz = N2 + 2 * P;
+            const int64_t strx = vw.xcopy ? 4 : 4 * Sz, stry = vw.xcopy ? 4 * Sx : 4 * Sz * Sx;
+            const int64_t str[3] = {vw.yorder ? stry : strx, vw.yorder ? strx : stry, vw.xcopy ? 4 * Sx * Sy : 4};
+            const Off last = (Off)(str[0] * (N[0] + 2 * P - NB) + str[1] * (N[1] + 2 * P - NB) +
+                                   str[2] * (N[2] + 2 * P - NB));
+            // DDA state per axis: parameter of the next knot plane and its
+            // step, the cell's lower knot plane and its step, and the byte
+            // offset of the cell's coefficient block and its steps
+            double tmax[3], tdel[3], md[3], ms[3], wh[3];
+            Off os[3], off = 0;
+            {
+                int m[3];
+                // a point just past the entry (the entry lies on a knot plane)
+                const double tm0 = t0 + fmin(1e-6, 0.5 * (t1 - t0));
 #pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                const double zs = fma(tm0, L.w[k], z0[k]) - kap;
-                m[k] = (int)floor(fmin(fmax(zs, -8.0), (double)N[k] + 8.0));
-                if (L.w[k] > 0.0) {
-                    stp[k] = 1;
-                    tdel[k] = 1.0 / L.w[k];
-                    tmax[k] = ((double)(m[k] + 1) + kap - z0[k]) / L.w[k];
-                } else if (L.w[k] < 0.0) {
-                    stp[k] = -1;
-                    tdel[k] = -1.0 / L.w[k];
-                    tmax[k] = ((double)m[k] + kap - z0[k]) / L.w[k];
-                } else {
-                    stp[k] = 0;
-                    tdel[k] = 0.0;
-                    tmax[k] = 1e300;
+                for (int k = 0; k < 3; ++k) {
+                    const double zs = fma(tm0, L.w[k], z0[k]) - kap;
+                    m[k] = (int)floor(fmin(fmax(zs, -8.0), (double)N[k] + 8.0));
+                    md[k] = (double)m[k] + kap;
+                    wh[k] = 0.5 * L.w[k];
+                    if (L.w[k] > 0.0) {
+                        ms[k] = 1.0;
+                        os[k] = (Off)str[k];
+                        tdel[k] = 1.0 / L.w[k];
+                        tmax[k] = ((double)(m[k] + 1) + kap - z0[k]) / L.w[k];
+                    } else if (L.w[k] < 0.0) {
+                        ms[k] = -1.0;
+                        os[k] = (Off)-str[k];
+                        tdel[k] = -1.0 / L.w[k];
+                        tmax[k] = ((double)m[k] + kap - z0[k]) / L.w[k];
+                    } else {
+                        ms[k] = 0.0;
+                        os[k] = 0;
+                        tdel[k] = 0.0;
+                        tmax[k] = 1e300;
+                    }
+                    off += (Off)((m[k] + qoff + P) * str[k]);
                 }
             }
-            // zero-padded copy of the coefficients (FWD_PAD(n) layers per side)
-            constexpr int P = FWD_PAD(n);
-            const int64_t s1 = N[0] + 2 * P, s2 = (int64_t)(N[0] + 2 * P) * (N[1] + 2 * P);
-            const int hi0 = N[0] - 1 + P - n, hi1 = N[1] - 1 + P - n, hi2 = N[2] - 1 + P - n;
+            // to the next knot plane of whichever axes reach theirs first:
+            // the walk ends after at most sum_k (N_k + 2h + 2) steps
             double tc = t0;
-            // every step moves one axis to its next knot plane: the walk ends
-            // after at most sum_k (N_k + 2h + 2) steps
-            while (tc < t1) {
-                int ax = 0;
-                double tn = tmax[0];
-                if (tmax[1] < tn) { tn = tmax[1]; ax = 1; }
-                if (tmax[2] < tn) { tn = tmax[2]; ax = 2; }
-                tn = fmin(tn, t1);
-                if (tn > tc) {
-                    const double mid = 0.5 * (tc + tn), half = 0.5 * (tn - tc);
+            auto advance = [&](double tn) {
+#pragma unroll
+                for (int k = 0; k < 3; ++k)
+                    if (tmax[k] <= tn) {
+                        asm volatile("");  // under a mask, not by selects
+                        tmax[k] += tdel[k];
+                        md[k] += ms[k];
+                        off += os[k];
+                    }
+            };
+            // the walk over a copy whose fastest axis is the contractions'
+            // third (z) or, XC, their first (x)
+            auto walk = [&](auto xc) {
+                constexpr bool XC = decltype(xc)::value;
+                // first element of each row of a block, in scalar registers
+                // (kept apart by the empty asm: one base and sixteen 64-bit
+                // vector additions per cell otherwise)
+                GlobalBytes rowp[NB][NB];
+#pragma unroll
+                for (int r1 = 0; r1 < NB; ++r1)
+#pragma unroll
+                    for (int r0 = 0; r0 < NB; ++r0) {
+                        rowp[r1][r0] = XC ? (GlobalBytes)cx + (r1 * str[2] + r0 * str[1])
+                                          : (GlobalBytes)cz + (r1 * str[1] + r0 * str[0]);
+                        asm("" : "+s"(rowp[r1][r0]));
+                    }
+                // the unit between parameters ta and tb of the cell with
+                // lower knot planes cm and block offset o; returns its
+                // term's two factors
+                auto unit = [&](double ta, double tb, const double cm[3], Off o, float &len) {
+                    // every cell of the walk lies in the support-padded box
+                    // or one cell beyond it, so its block is inside the copy;
+                    // the clamp only guards the address
+                    const Off ob = o < last ? o : last;
+                    float cb[NB][NB][NB];
+#pragma unroll
+                    for (int r1 = 0; r1 < NB; ++r1)
+#pragma unroll
+                        for (int r0 = 0; r0 < NB; ++r0) {
+                            const auto row = (GlobalFloats)(rowp[r1][r0] + ob);
+#pragma unroll
+                            for (int q = 0; q < NB; ++q) (XC ? cb[r1][r0][q] : cb[q][r1][r0]) = row[q];
+                        }
+                    // all loads first: spread over the integral they would
+                    // each be waited for (184 against 163 ms)
+                    __builtin_amdgcn_sched_barrier(0);
+                    // mid-point and half-length in the line's parameter, the
+                    // factor 1/2 carried by wh (and in cell_integral)
+                    const double sum = ta + tb, dif = tb - ta;
                     float lc[3], dl[3];
-                    int q0[3];
 #pragma unroll
                     for (int k = 0; k < 3; ++k) {
-                        lc[k] = (float)(fma(mid, L.w[k], z0[k]) - ((double)m[k] + kap));
-                        dl[k] = (float)(half * L.w[k]);
-                        q0[k] = m[k] + qoff;
+                        lc[k] = (float)(fma(sum, wh[k], z0[k]) - cm[k]);
+                        dl[k] = (float)(dif * wh[k]);
                     }
-                    // coefficient block from the padded copy: every cell of the
-                    // walk lies in the support-padded box, so its block is inside
-                    // the copy (the clamp only guards a cell index rounded past
-                    // the box edge, whose segment has no length)
-                    float cb[NB][NB][NB];
-                    {
-                        const int x0 = min(max(q0[0], -P), hi0) + P, x1 = min(max(q0[1], -P), hi1) + P,
-                                  x2 = min(max(q0[2], -P), hi2) + P;
-                        const float *base = cp + (int64_t)x2 * s2 + (int64_t)x1 * s1 + x0;
-#pragma unroll
-                        for (int a3 = 0; a3 < NB; ++a3)
-#pragma unroll
-                            for (int a2 = 0; a2 < NB; ++a2)
-#pragma unroll
-                                for (int a1 = 0; a1 < NB; ++a1) cb[a3][a2][a1] = base[a3 * s2 + a2 * s1 + a1];
-                    }
-                    float seg = 0.0f;
-#pragma unroll
-                    for (int l = 0; l < Rule::m; ++l) {
-                        const float xi = Rule::x(l);
-                        float w1[NB], w2[NB], w3[NB];
-                        cell_weights<n>(fmaf(dl[0], xi, lc[0]), w1);
-                        cell_weights<n>(fmaf(dl[1], xi, lc[1]), w2);
-                        cell_weights<n>(fmaf(dl[2], xi, lc[2]), w3);
-                        float f = 0.0f;
-#pragma unroll
-                        for (int a3 = 0; a3 < NB; ++a3) {
-                            float g = 0.0f;
-#pragma unroll
-                            for (int a2 = 0; a2 < NB; ++a2) {
-                                float r = 0.0f;
-#pragma unroll
-                                for (int a1 = 0; a1 < NB; ++a1) r = fmaf(w1[a1], cb[a3][a2][a1], r);
-                                g = fmaf(w2[a2], r, g);
-                            }
-                            f = fmaf(w3[a3], g, f);
+                    len = (float)dif;
+                    return cell_integral<n>(cb, lc, dl);
+                };
+                if constexpr (LPL == 1) {
+                    while (tc < t1) {
+                        const double tn = min64(min64(tmax[0], tmax[1]), tmax[2]), te = min64(tn, t1);
+                        if (te > tc) {
+                            float len;
+                            const float seg = unit(tc, te, md, off, len);
+                            acc = fmaf(len, seg, acc);
+                            tc = te;
                         }
-                        seg = fmaf(Rule::w(l), f, seg);
+                        advance(tn);
                     }
-                    acc = fmaf((float)half, seg, acc);
+                } else {
+                    while (tc < t1) {
+                        // the next four units of the line, one for each lane
+                        int got = 0;
+                        double ua = 0.0, ub = 0.0, um[3] = {0.0, 0.0, 0.0};
+                        Off uo = 0;
+                        while (tc < t1 && got < LPL) {
+                            const double tn = min64(min64(tmax[0], tmax[1]), tmax[2]), te = min64(tn, t1);
+                            if (te > tc) {
+                                if (got == sub) {
+                                    ua = tc;
+                                    ub = te;
+                                    um[0] = md[0]; um[1] = md[1]; um[2] = md[2];
+                                    uo = off;
+                                }
+                                ++got;
+                                tc = te;
+                            }
+                            advance(tn);
+                        }
+                        float len = 0.0f, seg = 0.0f;
+                        if (sub < got) seg = unit(ua, ub, um, uo, len);
+                        acc = got > 0 ? fmaf(quad_lane<0>(len), quad_lane<0>(seg), acc) : acc;
+                        acc = got > 1 ? fmaf(quad_lane<1>(len), quad_lane<1>(seg), acc) : acc;
+                        acc = got > 2 ? fmaf(quad_lane<2>(len), quad_lane<2>(seg), acc) : acc;
+                        acc = got > 3 ? fmaf(quad_lane<3>(len), quad_lane<3>(seg), acc) : acc;
+                    }
                 }
-                tc = fmax(tc, tn);
-                // advance the axis whose plane was reached
-                if (ax == 0) { m[0] += stp[0]; tmax[0] += tdel[0]; }
-                else if (ax == 1) { m[1] += stp[1]; tmax[1] += tdel[1]; }
-                else { m[2] += stp[2]; tmax[2] += tdel[2]; }
-            }
+            };
+            if (vw.xcopy) walk(std::true_type{});
+            else walk(std::false_type{});
         }
     }
-    y[((int64_t)v * R + j) * C + i] = acc;
+    if (sub == 0) y[((int64_t)v * R + j) * C + i] = acc;
 }
 
 // ---------------------------------------------------------------------------
@@ -850,42 +1013,48 @@ __global__ void xpay_kernel(const double *__restrict__ beta, const float *__rest
 // ---------------------------------------------------------------------------
 // host-side launchers
 // ---------------------------------------------------------------------------
+template <int n, int LPL, bool WIDE>
+static void launch_walk(const LaunchArgs &a, const float *cz, const float *cx, int which, hipStream_t st) {
+    const int tR = (a.R + 15) / 16, tC = (a.C + 15) / 16;
+    const int64_t nb = LPL == 1 ? fwd_blocks(tR, tC, a.V) : (int64_t)tR * tC * a.V * LPL;
+    hipLaunchKernelGGL((project_kernel<n, LPL, WIDE>), dim3((unsigned)nb), dim3(256), 0, st, cz, cx, a.N[0], a.N[1],
+                       a.N[2], a.geom, a.kind, a.V, a.R, a.C, a.sino, which);
+}
+
 template <int n>
 static hipError_t launch_project_n(const LaunchArgs &a, hipStream_t st) {
-    const int tR = (a.R + 15) / 16, tC = (a.C + 15) / 16;
-    const int nb = (int)fwd_blocks(tR, tC, a.V);
     constexpr int P = FWD_PAD(n);
-    const int64_t padded = (int64_t)(a.N[0] + 2 * P) * (a.N[1] + 2 * P) * (a.N[2] + 2 * P);
+    const int64_t Sx = a.N[0] + 2 * P, Sy = a.N[1] + 2 * P, Sz = a.N[2] + 2 * P, padded = Sx * Sy * Sz;
     if (!a.scratch || a.scratch_floats < padded) return hipErrorInvalidValue;
-    const int pb = (int)std::min<int64_t>((padded + 255) / 256, 65536);
-    hipLaunchKernelGGL(pad_volume_kernel, dim3(pb), dim3(256), 0, st, a.coeffs, a.N[0], a.N[1], a.N[2], P,
-                       a.scratch);
-    // Occupancy of the walk: for degrees 1..3 a block reserves LDS it does
-    // not use (FWD_IDLE_LDS), so that at most three blocks, three waves per
-    // SIMD, share a CU.  Fewer concurrent walks then share the CU's L1
-    // cache, which keeps more of each wave's coefficient rows; the degree-0
-    // walk (one coefficient per cell) runs best at full occupancy.
-    constexpr int FWD_IDLE_LDS = n == 0 ? 0 : 50 * 1024;  // 3 x 50 KiB of the CU's 160 KiB
-    hipLaunchKernelGGL(project_kernel<n>, dim3(nb), dim3(256), FWD_IDLE_LDS, st, a.scratch, a.N[0], a.N[1],
-                       a.N[2], a.geom, a.kind, a.V, a.R, a.C, a.sino, 0);
-    if constexpr (n >= 1) {
-        // the views that walk the y-fastest copy: the same scratch, rewritten
-        // after the first launch (stream order); the degree-0 walk, bound by
-        // L2 refills rather than by its arithmetic, keeps one copy
-        const int64_t yb = (int64_t)((a.N[0] + 2 * P + PAD_T - 1) / PAD_T) * ((a.N[1] + 2 * P + PAD_T - 1) / PAD_T) *
-                           (a.N[2] + 2 * P);
-        if (yb > INT32_MAX) return hipErrorInvalidValue;
-        hipLaunchKernelGGL(pad_volume_yfast_kernel, dim3((unsigned)yb), dim3(256), 0, st, a.coeffs, a.N[0], a.N[1],
-                           a.N[2], P, a.scratch);
-        hipLaunchKernelGGL(project_kernel<n>, dim3(nb), dim3(256), FWD_IDLE_LDS, st, a.scratch, a.N[0], a.N[1],
-                           a.N[2], a.geom, a.kind, a.V, a.R, a.C, a.sino, 1);
-    }
+    const int64_t zb = ((Sx + PAD_T - 1) / PAD_T) * ((Sz + PAD_T - 1) / PAD_T) * Sy;
+    if (zb > INT32_MAX) return hipErrorInvalidValue;
+    const auto walk = [&](const float *cz, const float *cx, int which) {
+        if (padded > (int64_t)1 << 30) launch_walk<n, 1, true>(a, cz, cx, which, st);
+        else if ((int64_t)((a.R + 15) / 16) * ((a.C + 15) / 16) * a.V <= FWD_SHARED_TILES)
+            launch_walk<n, 4, false>(a, cz, cx, which, st);
+        else launch_walk<n, 1, false>(a, cz, cx, which, st);
+    };
+    // the x-fastest copy beside the z-fastest one, or, where the scratch
+    // holds one, in its place after a launch for the views of the other
+    // (stream order)
+    const bool both = a.scratch_floats >= 2 * padded;
+    float *cz = a.scratch, *cx = both ? a.scratch + padded : a.scratch;
+    hipLaunchKernelGGL(pad_volume_zfast_kernel, dim3((unsigned)zb), dim3(256), 0, st, a.coeffs, a.N[0], a.N[1], a.N[2],
+                       P, cz);
+    if (!both) walk(cz, cx, 0);
+    hipLaunchKernelGGL(pad_volume_kernel, dim3((unsigned)std::min<int64_t>((padded + 255) / 256, 65536)), dim3(256), 0,
+                       st, a.coeffs, a.N[0], a.N[1], a.N[2], P, cx);
+    walk(cz, cx, both ? 2 : 1);
     return hipGetLastError();
 }
 
 int64_t project_quad_scratch_floats(int degree, const int N[3]) {
     const int64_t P = degree + 1;
     return (N[0] + 2 * P) * (N[1] + 2 * P) * (N[2] + 2 * P);
+}
+
+int project_quad_copies(int degree, const int N[3]) {
+    return project_quad_scratch_floats(degree, N) <= FWD_BOTH_FLOATS ? 2 : 1;
 }
 
 int64_t backproject_quad_scratch_floats(int degree, const int N[3], int64_t limit) {

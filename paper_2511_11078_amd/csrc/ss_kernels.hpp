@@ -48,6 +48,9 @@ int64_t backproject_quad_scratch_floats(int degree, const int N[3], int64_t limi
 // Zero-padded copy of the coefficients the quadrature forward walks.
 #define FWD_PAD(n) ((n) + 1)
 int64_t project_quad_scratch_floats(int degree, const int N[3]);
+// Copies of that size the forward uses if the scratch holds them (one is
+// enough; with two, one launch walks every view).
+int project_quad_copies(int degree, const int N[3]);
 
 hipError_t launch_project_quad(int degree, const LaunchArgs &a, hipStream_t st);
 
