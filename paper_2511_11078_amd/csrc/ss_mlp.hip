@@ -30,7 +30,7 @@ namespace ss {
 constexpr int HID = 64;
 
 // Weight image, kept in LDS by the kernels (27.4 KB).
-struct MlpImage {
+struct alignas(16) MlpImage {
     float w1a[2][3][64];       // layer-1 A operand: [row block][K step][lane]
     float bias[4][2][32];      // [layer][lane half][block * 16 + reg]
     uint32_t wh[3][2][4][64][4];  // hidden A operands: 8 bf16 per lane
@@ -135,7 +135,10 @@ ss_status mlp_blob_to_image(const void *blob, size_t bytes, int degree, std::vec
 // ---------------------------------------------------------------------------
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 // s(A) = A / (1 + 2^A) for A = -log2(e) z: the SiLU of z is -ln(2) s(A),
 // the factor being folded into the next layer's weights (see the image)
@@ -147,6 +150,35 @@ __device__ __forceinline__ void load_image(MlpImage &dst, const MlpImage *__rest
     uint4 *d = reinterpret_cast<uint4 *>(&dst);
     constexpr int n16 = sizeof(MlpImage) / 16;
     for (int i = threadIdx.x; i < n16; i += blockDim.x) d[i] = s[i];
+}
+
+// Two activations as the sum of two BF16 pairs: hi = RNE(a) and lo =
+// RNE(a - hi), each pair in one register.  hi is unpacked from its packed
+// form (a shift and a mask; the empty asm keeps the compiler from converting
+// each activation a second time instead: 1,920 against 2,197 VALU
+// instructions per pair with the 16-byte reads of the weight image, 32 views
+// at 128^3 97 -> 84 ms forward, 93 -> 80 ms adjoint).
+__device__ __forceinline__ void split_bf16(float a0, float a1, uint32_t &hi, uint32_t &lo) {
+    const f32x2 a = {a0, a1};
+    uint32_t h = __builtin_bit_cast(uint32_t, __builtin_convertvector(a, bf16x2));
+    asm("" : "+v"(h));
+    const f32x2 rest = {a0 - __uint_as_float(h << 16), a1 - __uint_as_float(h & 0xffff0000u)};
+    hi = h;
+    lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(rest, bf16x2));
+}
+
+// Accumulator start of layer L: its biases.
+__device__ __forceinline__ void load_bias(const MlpImage &W, int L, int hf, f32x16 &acc0, f32x16 &acc1) {
+    const f32x4 *b = reinterpret_cast<const f32x4 *>(W.bias[L][hf]);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const f32x4 v0 = b[q], v1 = b[4 + q];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            acc0[4 * q + r] = v0[r];
+            acc1[4 * q + r] = v1[r];
+        }
+    }
 }
 
 // Network value for the 32 pairs whose features sit in lanes base .. base+31
@@ -165,11 +197,7 @@ __device__ __forceinline__ float mlp_tile(const MlpImage &W, float f0, float f1,
         bop[2] = hf ? 0.0f : a4;
     }
     f32x16 acc0, acc1;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        acc0[r] = W.bias[0][hf][r];
-        acc1[r] = W.bias[0][hf][16 + r];
-    }
+    load_bias(W, 0, hf, acc0, acc1);
 #pragma unroll
     for (int kk = 0; kk < 3; ++kk) {
         acc0 = __builtin_amdgcn_mfma_f32_32x32x2f32(W.w1a[0][kk][lane], bop[kk], acc0, 0, 0, 0);
@@ -177,32 +205,30 @@ __device__ __forceinline__ float mlp_tile(const MlpImage &W, float f0, float f1,
     }
 #pragma unroll
     for (int L = 0; L < 3; ++L) {
-        // each activation as the sum of two BF16 numbers: hi = RNE(a),
-        // lo = RNE(a - hi); the layer is W hi + W lo in one FP32 accumulator
-        bf16x8 Bh[4], Bl[4];
+        // K step by K step: eight activations, each as the sum of two BF16
+        // numbers, and the layer's W hi + W lo in one FP32 accumulator
+        f32x16 n0, n1;
+        load_bias(W, L + 1, hf, n0, n1);
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk) {
-            f32x8 v;
+            uint4 Bh, Bl;
+            float v[8];
 #pragma unroll
             for (int e = 0; e < 8; ++e) v[e] = silu(kk < 2 ? acc0[8 * kk + e] : acc1[8 * (kk - 2) + e]);
-            Bh[kk] = __builtin_convertvector(v, bf16x8);
-            const f32x8 back = __builtin_convertvector(Bh[kk], f32x8);
-            Bl[kk] = __builtin_convertvector(v - back, bf16x8);
+            split_bf16(v[0], v[1], Bh.x, Bl.x);
+            split_bf16(v[2], v[3], Bh.y, Bl.y);
+            split_bf16(v[4], v[5], Bh.z, Bl.z);
+            split_bf16(v[6], v[7], Bh.w, Bl.w);
+            const bf16x8 A0 = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(W.wh[L][0][kk][lane]));
+            const bf16x8 A1 = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(W.wh[L][1][kk][lane]));
+            const bf16x8 H = __builtin_bit_cast(bf16x8, Bh), Lo = __builtin_bit_cast(bf16x8, Bl);
+            n0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A0, H, n0, 0, 0, 0);
+            n1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A1, H, n1, 0, 0, 0);
+            n0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A0, Lo, n0, 0, 0, 0);
+            n1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A1, Lo, n1, 0, 0, 0);
         }
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            acc0[r] = W.bias[L + 1][hf][r];
-            acc1[r] = W.bias[L + 1][hf][16 + r];
-        }
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk) {
-            const bf16x8 A0 = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(W.wh[L][0][kk][lane]));
-            const bf16x8 A1 = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(W.wh[L][1][kk][lane]));
-            acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A0, Bh[kk], acc0, 0, 0, 0);
-            acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A1, Bh[kk], acc1, 0, 0, 0);
-            acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A0, Bl[kk], acc0, 0, 0, 0);
-            acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A1, Bl[kk], acc1, 0, 0, 0);
-        }
+        acc0 = n0;
+        acc1 = n1;
     }
     float part = 0.0f;
 #pragma unroll
@@ -214,15 +240,19 @@ __device__ __forceinline__ float mlp_tile(const MlpImage &W, float f0, float f1,
     return part + W.bout;
 }
 
-// Both tiles of a wave: each lane gets the value of its own pair.  The two
-// independent tiles are left to the scheduler, which interleaves one tile's
-// matrix-core work with the other's SiLU (24 views of cone_256: forward
-// 1,263 against 1,485 ms with a scheduling barrier between the tiles; the
-// adjoint, whose candidate state then spills, 1,237 against 1,394 ms).
+// Both tiles of a wave: each lane gets the value of its own pair.  What
+// bounds a round of 64 pairs is VALU issue: 512 transcendentals at half rate,
+// about 1,000 more operations of the SiLU and the split, 250 to 350 of the
+// search for pairs; the matrix cores are busy 30 % of the time.  The second
+// tile starts after the first (the empty asm): interleaved, the two need 235
+// registers in the forward and spill in the adjoint, and take 76.0 against
+// 72.8 ms and 86.8 against 80.0 ms (32 views at 128^3).
 __device__ __forceinline__ float mlp_wave(const MlpImage &W, const float f[5]) {
     const int lane = threadIdx.x & 63;
-    const float ra = mlp_tile(W, f[0], f[1], f[2], f[3], f[4], 0);
-    const float rb = mlp_tile(W, f[0], f[1], f[2], f[3], f[4], 32);
+    float ra = mlp_tile(W, f[0], f[1], f[2], f[3], f[4], 0);
+    float g[5] = {f[0], f[1], f[2], f[3], f[4]};
+    asm volatile("" : "+v"(ra), "+v"(g[0]), "+v"(g[1]), "+v"(g[2]), "+v"(g[3]), "+v"(g[4]));
+    const float rb = mlp_tile(W, g[0], g[1], g[2], g[3], g[4], 32);
     return lane < 32 ? ra : rb;
 }
 
@@ -277,7 +307,8 @@ __device__ __forceinline__ Fold make_fold(const double w[3]) {
 // its next (line, basis) pair with a non-empty chord, the wave evaluates the
 // 64 pairs on the matrix cores, and each lane accumulates c_q * f_theta.
 // ---------------------------------------------------------------------------
-template <int n>
+// STEP: slabs between two this walk visits.
+template <int n, int STEP = 1>
 struct Walk {
     double A1, A2, r1, r2, H1, H2;
     int j, j1, N1, N2, lo1, hi1, hi2, q1, q2;
@@ -300,15 +331,17 @@ struct Walk {
             q1 = lo1;
             ++q2;
             if (q2 > hi2 || lo1 > hi1) {
-                ++j;
+                j += STEP;
                 if (j <= j1) window();
             }
         }
     }
 };
 
-template <int n>
-__device__ __forceinline__ void walk_init(Walk<n> &W, const LineD &L, const int N[3], int &d, int &i1, int &i2) {
+// `first`: which of the line's first STEP slabs the walk starts at.
+template <int n, int STEP>
+__device__ __forceinline__ void walk_init(Walk<n, STEP> &W, const LineD &L, const int N[3], int first, int &d, int &i1,
+                                          int &i2) {
     constexpr double h = (double)Degree<n>::h;
     dominant_axis(L.w, d, i1, i2);
     const double wd = pick3(L.w, d);
@@ -337,7 +370,7 @@ __device__ __forceinline__ void walk_init(Walk<n> &W, const LineD &L, const int 
             jhi = fmin(jhi, ceil(fmax(ta, tb)));
         }
     }
-    W.j = (int)fmin(fmax(jlo, 0.0), (double)Nd);
+    W.j = (int)fmin(fmax(jlo, 0.0), (double)Nd) + first;
     W.j1 = (int)fmax(fmin(jhi, (double)(Nd - 1)), -1.0);
     const int64_t strides[3] = {1, (int64_t)N[0], (int64_t)N[0] * N[1]};
     W.sd = pick3(strides, d);
@@ -366,29 +399,33 @@ struct FwdPairBuf {
 // footprint to the owning lane's sum in LDS (atomic adds within the wave),
 // so rounds stay full while some lines of the wave are done and others are
 // not (about 6 % empty slots at cone_256 when each lane evaluated its own
-// pairs).
+// pairs).  The four waves of a network block take the same 8 x 8 lines, each
+// every fourth slab of them, and their sums are added in the waves' order:
+// four times as many, shorter blocks, tiles innermost (32^3, 32 views of
+// 48 x 48: 15.5 -> 3.7 ms; 32 views at 128^3: 84 -> 73 ms).
 template <int n, bool EXACT>
 __device__ __forceinline__ void project_walk(const float *__restrict__ c, int N0, int N1, int N2,
                                              const float *__restrict__ geom, int kind, int V, int R, int C,
                                              const MlpImage *Wt, float *__restrict__ y, int v, int tr, int tc,
-                                             FwdPairBuf *fbuf = nullptr, float *accw = nullptr) {
+                                             int part = 0, FwdPairBuf *fbuf = nullptr, float *accw = nullptr) {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int j = tr * 16 + (wave >> 1) * 8 + (lane >> 3);
-    const int i = tc * 16 + (wave & 1) * 8 + (lane & 7);
+    const int quarter = EXACT ? wave : part;  // 8 x 8 pixels of the 16 x 16 tile
+    const int j = tr * 16 + (quarter >> 1) * 8 + (lane >> 3);
+    const int i = tc * 16 + (quarter & 1) * 8 + (lane & 7);
     const bool pix = v < V && j < R && i < C;
     const int N[3] = {N0, N1, N2};
     const double centre[3] = {0.0, 0.0, 0.0};
     LineD L;
     L.ok = false;
     if (pix) L = make_line(geom + 12 * v, kind, R, C, j, i, centre);
-    Walk<n> Wk;
+    Walk<n, EXACT ? 1 : 4> Wk;
     int d = 0, i1 = 1, i2 = 2;
     Fold F;
     Slopes S;
     float inv_wd = 0.0f;
     bool live = false;
     if (L.ok) {
-        walk_init<n>(Wk, L, N, d, i1, i2);
+        walk_init(Wk, L, N, EXACT ? 0 : wave, d, i1, i2);
         F = make_fold(L.w);
         S = make_slopes((float)Wk.r1, (float)Wk.r2);
         inv_wd = (float)(1.0 / fabs(pick3(L.w, d)));
@@ -429,11 +466,16 @@ __device__ __forceinline__ void project_walk(const float *__restrict__ c, int N0
                                        __HIP_MEMORY_SCOPE_WORKGROUP);
         }
     };
+    // exact form: each round every lane advances to its next pair.  Network
+    // form: each round every lane tests one candidate and the pairs found are
+    // buffered; 64 at a time are evaluated, the last ones when no lane has
+    // any left
     while (true) {
         bool have = false;
         float u1 = 0.0f, u2 = 0.0f;
         int64_t idx = 0;
-        while (live && !have) {
+        const bool any = EXACT || __ballot(live) != 0;
+        for (bool go = live; go; go = EXACT && live && !have) {
             if (Wk.valid()) {
                 const double P1 = fma((double)Wk.j, Wk.r1, Wk.A1), P2 = fma((double)Wk.j, Wk.r2, Wk.A2);
                 u1 = (float)(P1 - (double)Wk.q1);
@@ -447,8 +489,8 @@ __device__ __forceinline__ void project_walk(const float *__restrict__ c, int N0
             live = !Wk.done();
         }
         const uint64_t m = __ballot(have);
-        if (m == 0) break;
         if constexpr (EXACT) {
+            if (m == 0) break;
             const float fp = have ? footprint_slab<n>(S, u1, u2) * inv_wd : 0.0f;
             if (have) acc = fmaf(c[idx], fp, acc);
         } else {
@@ -467,36 +509,39 @@ __device__ __forceinline__ void project_walk(const float *__restrict__ c, int N0
                 B.owner[slot] = lane;
             }
             wcount += __popcll(m);
-            if (wcount >= 64) {
-                flush(64);
-                head = (head + 64) & (FBUF - 1);
-                wcount -= 64;
+            if (wcount >= 64 || (!any && wcount > 0)) {
+                const int cnt = min(wcount, 64);
+                flush(cnt);
+                head = (head + cnt) & (FBUF - 1);
+                wcount -= cnt;
             }
+            if (!any && wcount == 0) break;
         }
     }
     if constexpr (!EXACT) {
-        if (wcount > 0) flush(wcount);
-        acc = accw[threadIdx.x];
+        __syncthreads();
+        acc = ((accw[lane] + accw[lane + 64]) + accw[lane + 128]) + accw[lane + 192];
+        if (wave != 0) return;
     }
     if (pix) y[((int64_t)v * R + j) * C + i] = acc;
 }
 
-// two workgroups (eight waves) per CU: one wave's matrix-core layers overlap
-// another's SiLU
+// three workgroups (twelve waves) per CU: one wave's matrix-core layers
+// overlap another's SiLU
 template <int n>
-__global__ void __launch_bounds__(256, 2) project_mlp_kernel(const float *__restrict__ c, int N0, int N1, int N2,
+__global__ void __launch_bounds__(256, 3) project_mlp_kernel(const float *__restrict__ c, int N0, int N1, int N2,
                                                           const float *__restrict__ geom, int kind, int V, int R,
                                                           int C, const MlpImage *__restrict__ img,
                                                           float *__restrict__ y) {
     __shared__ MlpImage Wt;
     __shared__ FwdPairBuf fbuf[4];  // one ring per wave of the 256-thread block
     __shared__ float accw[256];
+    // four blocks per 16 x 16-pixel tile, views outermost
     const int tR = (R + 15) / 16, tC = (C + 15) / 16;
-    int v, tr, tc;
-    if (!fwd_block_tile(V, tR, tC, v, tr, tc)) return;  // padding slot: the whole block
+    const int part = blockIdx.x & 3, t = blockIdx.x >> 2, tc = t % tC, tr = (t / tC) % tR, v = t / (tC * tR);
     load_image(Wt, img);
     __syncthreads();
-    project_walk<n, false>(c, N0, N1, N2, geom, kind, V, R, C, &Wt, y, v, tr, tc, fbuf, accw);
+    project_walk<n, false>(c, N0, N1, N2, geom, kind, V, R, C, &Wt, y, v, tr, tc, part, fbuf, accw);
 }
 
 template <int n>
@@ -513,8 +558,19 @@ __global__ void __launch_bounds__(256) project_pair_kernel(const float *__restri
 // Adjoint, network form: the brick gather of the quadrature kernel with the
 // per-line fold data added to the LDS table.
 // ---------------------------------------------------------------------------
-constexpr int MBX = 8, MBY = 8, MBZ = 4;
-constexpr int MRAY_CAP = 384;
+// Brick of coefficients of a block, and lines in its table.  Large: one
+// coefficient per thread.  Small (network form, volumes of few large bricks):
+// one per lane, the block's four waves taking every fourth candidate pixel of
+// each, so that there are four times as many blocks.
+template <bool SMALL> struct Brick {
+    static constexpr int X = SMALL ? 4 : 8, Y = SMALL ? 4 : 8, Z = 4, waves = SMALL ? 4 : 1;
+    static constexpr int lines = SMALL ? 256 : 384;
+};
+// Largest volume, in large bricks, that takes small ones: with 512 blocks on
+// the chip at a time, 32^3 takes 2.3 ms in small and 5.2 in large bricks (128
+// of them), 56^3 7.8 and 8.3 (686), 64^3 11.3 and 10.6 (1,024), 128^3 89 and
+// 80; a small brick sets up 2.6 times as many lines per coefficient.
+constexpr int SMALL_BRICKS = 768;
 constexpr float MPIX_MARGIN = 1.0e-3f;  // pixels
 
 struct RayRecM {     // 80 bytes
@@ -567,18 +623,20 @@ __device__ __forceinline__ void fill_ray_m(RayRecM &rec, const float *__restrict
 // times the footprint to the owners' sums in LDS (atomic adds within the
 // wave, since owner and evaluating lane differ): every round is full, and
 // pairs carry over from one chunk or view to the next.
-template <int n, bool EXACT>
+template <int n, bool EXACT, bool SMALL>
 __device__ __forceinline__ void backproject_gather(const float *__restrict__ y, int N0, int N1, int N2,
                                                    const float *__restrict__ geom, const ViewProj *__restrict__ vps,
                                                    int kind, int V, int R, int C, const MlpImage *Wt,
                                                    RayRecM *rays, ViewProj &vp, LocalProj &lp, int *sbox,
                                                    PairBuf *pbuf, float *accw, float *__restrict__ c) {
     constexpr float hf = Degree<n>::h;
+    constexpr int MBX = Brick<SMALL>::X, MBY = Brick<SMALL>::Y, MBZ = Brick<SMALL>::Z;
+    constexpr int MRAY_CAP = Brick<SMALL>::lines, WAVES = Brick<SMALL>::waves;
     const int nbx = (N0 + MBX - 1) / MBX, nby = (N1 + MBY - 1) / MBY, nbz = (N2 + MBZ - 1) / MBZ;
     const int b = xcd_remap(blockIdx.x, nbx * nby * nbz);
     const int bx = b % nbx, by = (b / nbx) % nby, bz = b / (nbx * nby);
-    const int tid = threadIdx.x;
-    const int k0 = bx * MBX + (tid % MBX), k1 = by * MBY + ((tid / MBX) % MBY), k2 = bz * MBZ + tid / (MBX * MBY);
+    const int tid = threadIdx.x, own = tid % (256 / WAVES), first = tid / (256 / WAVES);
+    const int k0 = bx * MBX + (own % MBX), k1 = by * MBY + ((own / MBX) % MBY), k2 = bz * MBZ + own / (MBX * MBY);
     const bool mine = k0 < N0 && k1 < N1 && k2 < N2;
     constexpr double h = (double)Degree<n>::h;
     const double o[3] = {-0.5 * (N0 - 1), -0.5 * (N1 - 1), -0.5 * (N2 - 1)};
@@ -609,16 +667,22 @@ __device__ __forceinline__ void backproject_gather(const float *__restrict__ y, 
             const int e = (head + lane) & (PBUF - 1);
             const float f[5] = {B.v[0][e], B.v[1][e], B.v[2][e], B.v[3][e], B.v[4][e]};
             const float yv = B.v[5][e];
-            const int own = B.owner[e];
+            const int who = B.owner[e];
             const float fp = mlp_wave(*Wt, f);
             if (lane < cnt)
-                __hip_atomic_fetch_add(&accw[own], yv * fp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                __hip_atomic_fetch_add(&accw[who], yv * fp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         }
     };
-    for (int v = 0; v < V; ++v) {
+    // the network form goes round once more after the last view, with no
+    // candidates, to evaluate the pairs that are left
+    for (int v = 0; v < (EXACT ? V : V + 1); ++v) {
+        const bool rest = !EXACT && v == V;
         const float *e = geom + 12 * v;
         __syncthreads();
-        if (tid == 0) {
+        if (tid == 0 && rest) {
+            sbox[0] = sbox[2] = 0;
+            sbox[1] = sbox[3] = 0;
+        } else if (tid == 0) {
             vp = vps[v];
             make_localproj(vp, centre, lp);
             double lo[3], hi[3];
@@ -669,7 +733,7 @@ __device__ __forceinline__ void backproject_gather(const float *__restrict__ y, 
             for (int ci0 = bi0; ci0 <= bi1; ci0 += cols) {
                 const int ci1 = min(bi1, ci0 + cols - 1);
                 const int cw = ci1 - ci0 + 1;
-                const int cn = (cj1 - cj0 + 1) * cw;
+                const int cn = rest ? 0 : (cj1 - cj0 + 1) * cw;
                 __syncthreads();
                 for (int t = tid; t < cn; t += blockDim.x) {
                     const int jj = cj0 + t / cw, ii = ci0 + t % cw;
@@ -679,8 +743,15 @@ __device__ __forceinline__ void backproject_gather(const float *__restrict__ y, 
                 // this thread's pixels inside the chunk, visited row-major
                 const int j0 = mine ? max(mj0, cj0) : 1, j1 = mine ? min(mj1, cj1) : 0;
                 const int i0 = max(mi0, ci0), i1 = min(mi1, ci1);
-                int jj = j0, ii = i0;
-                bool live = j0 <= j1 && i0 <= i1;
+                int jj = j0, ii = i0 + first;
+                bool live = j0 <= j1 && i0 <= i1 && !rest;
+                const int ni = i1 - i0 + 1;
+                // to the pixel WAVES further on
+                const auto wrap = [&] {
+                    while (ii > i1 && jj <= j1) { ii -= ni; ++jj; }
+                    live = live && jj <= j1;
+                };
+                if (live) wrap();
                 if constexpr (EXACT) {
                     // every round each lane with pixels left evaluates its next pair
                     while (true) {
@@ -704,21 +775,21 @@ __device__ __forceinline__ void backproject_gather(const float *__restrict__ y, 
                                 PS = S;
                                 iwd = rr.iwd;
                             }
-                            ++ii;
-                            if (ii > i1) { ii = i0; ++jj; }
-                            live = jj <= j1;
+                            ii += WAVES;
+                            wrap();
                         }
                         if (__ballot(have) == 0) break;
                         const float fp = have ? footprint_slab<n>(PS, pu1, pu2) * iwd : 0.0f;
                         if (have) acc = fmaf(yv, fp, acc);
                     }
                 } else {
-                    // every round each lane with pixels left finds its next
-                    // pair; the found pairs go into the ring (at most 63 + 64)
+                    // every round each lane with pixels left tests one; the
+                    // pairs found go into the ring (at most 63 + 64)
                     while (true) {
                         bool have = false;
                         float pv[6];
-                        while (live && !have) {
+                        const bool any = __ballot(live) != 0;
+                        if (live) {
                             const RayRecM &rr = rays[(jj - cj0) * cw + (ii - ci0)];
                             const int d = rr.d;
                             const int i1x = d == 0 ? 1 : 0, i2x = d == 2 ? 1 : 2;
@@ -735,12 +806,10 @@ __device__ __forceinline__ void backproject_gather(const float *__restrict__ y, 
                                 pv[4] = fmaf(rr.V[0], x0, fmaf(rr.V[1], x1, rr.V[2] * x2));
                                 pv[5] = rr.y;
                             }
-                            ++ii;
-                            if (ii > i1) { ii = i0; ++jj; }
-                            live = jj <= j1;
+                            ii += WAVES;
+                            wrap();
                         }
                         const uint64_t m = __ballot(have);
-                        if (m == 0) break;  // every lane has exhausted this chunk
                         if (have) {
                             PairBuf &B = pbuf[tid >> 6];
                             const int rank = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
@@ -751,38 +820,44 @@ __device__ __forceinline__ void backproject_gather(const float *__restrict__ y, 
                             B.owner[slot] = tid;
                         }
                         wcount += __popcll(m);
-                        if (wcount >= 64) {
-                            flush(64);
-                            head = (head + 64) & (PBUF - 1);
-                            wcount -= 64;
+                        if (wcount >= 64 || (rest && wcount > 0)) {
+                            const int cnt = min(wcount, 64);
+                            flush(cnt);
+                            head = (head + cnt) & (PBUF - 1);
+                            wcount -= cnt;
                         }
+                        if (!any && !(rest && wcount > 0)) break;  // every lane has exhausted this chunk
                     }
                 }
             }
         }
     }
     if constexpr (!EXACT) {
-        if (wcount > 0) flush(wcount);
-        acc = accw[tid];  // the wave's atomic adds precede this read (LDS operations of a wave run in order)
+        __syncthreads();
+        acc = accw[own];
+        if constexpr (SMALL) {
+            acc = ((acc + accw[own + 64]) + accw[own + 128]) + accw[own + 192];
+            if (first != 0) return;
+        }
     }
     if (mine) c[((int64_t)k2 * N1 + k1) * N0 + k0] = acc;
 }
 
-template <int n>
+template <int n, bool SMALL>
 __global__ void __launch_bounds__(256, 2) backproject_mlp_kernel(const float *__restrict__ y, int N0, int N1, int N2,
                                                               const float *__restrict__ geom,
                                                               const ViewProj *__restrict__ vps, int kind, int V,
                                                               int R, int C, const MlpImage *__restrict__ img,
                                                               float *__restrict__ c) {
     __shared__ MlpImage Wt;
-    __shared__ RayRecM rays[MRAY_CAP];
+    __shared__ RayRecM rays[Brick<SMALL>::lines];
     __shared__ ViewProj vp;
     __shared__ LocalProj lp;
     __shared__ int sbox[4];
     __shared__ PairBuf pbuf[4];  // one ring per wave of the 256-thread block
     __shared__ float accw[256];
     load_image(Wt, img);
-    backproject_gather<n, false>(y, N0, N1, N2, geom, vps, kind, V, R, C, &Wt, rays, vp, lp, sbox, pbuf, accw, c);
+    backproject_gather<n, false, SMALL>(y, N0, N1, N2, geom, vps, kind, V, R, C, &Wt, rays, vp, lp, sbox, pbuf, accw, c);
 }
 
 template <int n>
@@ -790,11 +865,11 @@ __global__ void __launch_bounds__(256) backproject_pair_kernel(const float *__re
                                                                const float *__restrict__ geom,
                                                                const ViewProj *__restrict__ vps, int kind, int V,
                                                                int R, int C, float *__restrict__ c) {
-    __shared__ RayRecM rays[MRAY_CAP];
+    __shared__ RayRecM rays[Brick<false>::lines];
     __shared__ ViewProj vp;
     __shared__ LocalProj lp;
     __shared__ int sbox[4];
-    backproject_gather<n, true>(y, N0, N1, N2, geom, vps, kind, V, R, C, nullptr, rays, vp, lp, sbox, nullptr, nullptr,
+    backproject_gather<n, true, false>(y, N0, N1, N2, geom, vps, kind, V, R, C, nullptr, rays, vp, lp, sbox, nullptr, nullptr,
                                 c);
 }
 
@@ -845,16 +920,28 @@ __global__ void __launch_bounds__(64) footprint_mlp_kernel(const float *__restri
 template <int n>
 static hipError_t launch_project_mlp_n(const LaunchArgs &a, hipStream_t st) {
     const int tR = (a.R + 15) / 16, tC = (a.C + 15) / 16;
-    hipLaunchKernelGGL(project_mlp_kernel<n>, dim3((unsigned)fwd_blocks(tR, tC, a.V)), dim3(256), 0, st, a.coeffs, a.N[0], a.N[1],
+    hipLaunchKernelGGL(project_mlp_kernel<n>, dim3((unsigned)((int64_t)tR * tC * a.V * 4)), dim3(256), 0, st, a.coeffs, a.N[0], a.N[1],
                        a.N[2], a.geom, a.kind, a.V, a.R, a.C, (const MlpImage *)a.mlp, a.sino);
     return hipGetLastError();
 }
 
+template <bool SMALL>
+static int brick_count(const int N[3]) {
+    using B = Brick<SMALL>;
+    return ((N[0] + B::X - 1) / B::X) * ((N[1] + B::Y - 1) / B::Y) * ((N[2] + B::Z - 1) / B::Z);
+}
+
+template <int n, bool SMALL>
+static void launch_backproject_mlp_bricks(const LaunchArgs &a, hipStream_t st) {
+    hipLaunchKernelGGL((backproject_mlp_kernel<n, SMALL>), dim3(brick_count<SMALL>(a.N)), dim3(256), 0, st, a.sino_in,
+                       a.N[0], a.N[1], a.N[2], a.geom, a.vproj, a.kind, a.V, a.R, a.C, (const MlpImage *)a.mlp,
+                       a.coeffs_out);
+}
+
 template <int n>
 static hipError_t launch_backproject_mlp_n(const LaunchArgs &a, hipStream_t st) {
-    const int nb = ((a.N[0] + MBX - 1) / MBX) * ((a.N[1] + MBY - 1) / MBY) * ((a.N[2] + MBZ - 1) / MBZ);
-    hipLaunchKernelGGL(backproject_mlp_kernel<n>, dim3(nb), dim3(256), 0, st, a.sino_in, a.N[0], a.N[1], a.N[2],
-                       a.geom, a.vproj, a.kind, a.V, a.R, a.C, (const MlpImage *)a.mlp, a.coeffs_out);
+    if (brick_count<false>(a.N) <= SMALL_BRICKS) launch_backproject_mlp_bricks<n, true>(a, st);
+    else launch_backproject_mlp_bricks<n, false>(a, st);
     return hipGetLastError();
 }
 
@@ -868,7 +955,7 @@ static hipError_t launch_project_pair_n(const LaunchArgs &a, hipStream_t st) {
 
 template <int n>
 static hipError_t launch_backproject_pair_n(const LaunchArgs &a, hipStream_t st) {
-    const int nb = ((a.N[0] + MBX - 1) / MBX) * ((a.N[1] + MBY - 1) / MBY) * ((a.N[2] + MBZ - 1) / MBZ);
+    const int nb = brick_count<false>(a.N);
     hipLaunchKernelGGL(backproject_pair_kernel<n>, dim3(nb), dim3(256), 0, st, a.sino_in, a.N[0], a.N[1], a.N[2],
                        a.geom, a.vproj, a.kind, a.V, a.R, a.C, a.coeffs_out);
     return hipGetLastError();

@@ -1,0 +1,50 @@
+"""Block shapes of the network form against brute-force pair sums.
+
+Forward blocks take 8 x 8 lines, each of their four waves every fourth slab
+of them; adjoint blocks a brick of 4 x 4 x 4 coefficients, each wave every
+fourth candidate pixel of them, or, for more than 768 bricks of
+8 x 8 x 4, one such brick with a coefficient per thread.  Volumes and
+detectors at the edges of those shapes; the bars are those of the pair
+enumeration tests (2e-5 forward, 3e-5 for the adjoint of a noise sinogram).
+"""
+import numpy as np
+import pytest
+
+from paper_2511_11078_amd import footprint_net as fn
+from paper_2511_11078_amd.ops import Context, default_weights
+
+from gpu_helpers import rel_l2, say, tilted_parallel, to_gpu, to_np
+from test_gpu_mlp import _pairs_reference, _pairs_reference_adjoint
+
+pytestmark = pytest.mark.gpu
+
+CASES = {
+    # name: (dims, views, rows, cols, pitch)
+    "one_coefficient_one_line": ((1, 1, 1), 2, 1, 1, 1.0),
+    "one_slab": ((9, 7, 1), 2, 9, 3, 0.9),
+    "one_candidate_column": ((5, 4, 13), 3, 17, 1, 0.3),
+    "brick_edges": ((4, 8, 5), 3, 8, 9, 0.8),
+    "segments_of_the_line_table": ((5, 3, 4), 2, 40, 21, 0.25),
+    "last_small_brick_volume": ((64, 64, 48), 1, 5, 4, 3.0),   # 8 x 8 x 12 = 768 bricks
+    "first_large_brick_volume": ((64, 64, 49), 1, 4, 5, 3.0),  # 832
+}
+
+
+@pytest.mark.parametrize("case", list(CASES))
+def test_blocks_match_pair_enumeration(case):
+    dims, views, R, C, pitch = CASES[case]
+    say(f"network blocks {case} {dims}")
+    with open(default_weights(3), "rb") as fh:
+        blob = fn.parse_blob(fh.read())
+    rng = np.random.default_rng(500)
+    geom = tilted_parallel(views, R, C, seed=501, pitch=pitch)
+    c = rng.uniform(0.2, 1.0, dims[::-1]).astype(np.float32)
+    y = rng.standard_normal((views, R, C)).astype(np.float32)
+    ctx = Context(3, "mlp", 0)
+    got_f, got_b = to_np(ctx.project(to_gpu(c), geom)), to_np(ctx.backproject(to_gpu(y), geom, dims))
+    ctx.close()
+    want_f, want_b = _pairs_reference(blob, 3, c, geom), _pairs_reference_adjoint(blob, 3, y, geom, dims)
+    ef, eb = rel_l2(got_f, want_f), rel_l2(got_b, want_b)
+    say(f"  forward rel-L2 {ef:.3e}, adjoint rel-L2 {eb:.3e}")
+    assert np.abs(want_f).max() > 0 and np.abs(want_b).max() > 0
+    assert ef <= 2e-5 and eb <= 3e-5
