@@ -67,19 +67,19 @@ MLP_TRANS_PER_PAIR = 2 * 4 * 64   # SiLU of 4 x 64 hidden units: one exp and one
 # profiles/cone256_traffic_counters.md.  Valid only for the kernel sources they
 # were measured on (SHA-256 over QUAD_SOURCES); otherwise reported as null.
 QUAD_SOURCES = ["csrc/ss_kernels.hip", "csrc/ss_math.hpp", "csrc/ss_traverse.hpp", "csrc/ss_kernels.hpp"]
-TRAFFIC_SHA256 = "c580b437c23a8cebabf35f2db8d6132e404372d2385cfd0ecd7ec973b326af94"
+TRAFFIC_SHA256 = "055f8d65d185177885dc6de4f2fb0bc6bc7ceeb1415beaf6fdd59f6bc417fd1e"
 TRAFFIC_BYTES = {  # (kernel, degree) -> (read bytes, written bytes) per application, cone_256
-    ("pad_volume_kernel", 3): (2.0 * 36888 * 1024, 1.0 * 71874 * 1024),
-    ("pad_volume_zfast_kernel", 3): (2.0 * 65559 * 1024, 1.0 * 72259 * 1024),
+    ("pad_volume_kernel", 3): (2.0 * 36889 * 1024, 1.0 * 71874 * 1024),
+    ("pad_volume_zfast_kernel", 3): (2.0 * 65558 * 1024, 1.0 * 72249 * 1024),
     ("pad_volume_yfast_kernel", 3): (0.0, 0.0),  # a y-fastest copy is no longer made
-    ("project_kernel", 3): (2.0 * 3801477 * 1024, 1.0 * 255451 * 1024),
-    ("backproject_cells_kernel", 3): (2.0 * 3018571 * 1024, 1.0 * 5654054 * 1024),
-    ("cells_to_coeffs_kernel", 3): (2.0 * 2469840 * 1024, 1.0 * 65536 * 1024),
-    ("pad_volume_zfast_kernel", 0): (2.0 * 65561 * 1024, 1.0 * 80221 * 1024),
+    ("project_kernel", 3): (2.0 * 3801500 * 1024, 1.0 * 255417 * 1024),
+    ("backproject_cells_kernel", 3): (2.0 * 3018088 * 1024, 1.0 * 5623803 * 1024),
+    ("cells_to_coeffs_kernel", 3): (2.0 * 2449364 * 1024, 1.0 * 65536 * 1024),
+    ("pad_volume_zfast_kernel", 0): (2.0 * 65561 * 1024, 1.0 * 80217 * 1024),
     ("pad_volume_kernel", 0): (2.0 * 36888 * 1024, 1.0 * 67084 * 1024),
-    ("project_kernel", 0): (2.0 * 2964952 * 1024, 1.0 * 268032 * 1024),
-    ("backproject_cells_kernel", 0): (2.0 * 1251143 * 1024, 1.0 * 67642 * 1024),
-    ("cells_to_coeffs_kernel", 0): (2.0 * 32783 * 1024, 1.0 * 65536 * 1024),
+    ("project_kernel", 0): (2.0 * 2965582 * 1024, 1.0 * 267903 * 1024),
+    ("backproject_cells_kernel", 0): (2.0 * 1240164 * 1024, 1.0 * 67567 * 1024),
+    ("cells_to_coeffs_kernel", 0): (2.0 * 32788 * 1024, 1.0 * 65536 * 1024),
 }
 
 
@@ -92,13 +92,13 @@ L2_FILL_BYTES = {  # (kernel, degree) -> bytes per application, cone_256
     ("pad_volume_kernel", 3): 128.0 * 589824,
     ("pad_volume_zfast_kernel", 3): 128.0 * 1048576,
     ("pad_volume_yfast_kernel", 3): 0.0,
-    ("project_kernel", 3): 128.0 * 10405670636,
-    ("backproject_cells_kernel", 3): 128.0 * 270323721,
-    ("cells_to_coeffs_kernel", 3): 128.0 * 45318638,
+    ("project_kernel", 3): 128.0 * 10405279318,
+    ("backproject_cells_kernel", 3): 128.0 * 270358594,
+    ("cells_to_coeffs_kernel", 3): 128.0 * 45512386,
     ("pad_volume_zfast_kernel", 0): 128.0 * 1048576,
     ("pad_volume_kernel", 0): 128.0 * 589824,
-    ("project_kernel", 0): 128.0 * 2107709345,
-    ("backproject_cells_kernel", 0): 128.0 * 250920976,
+    ("project_kernel", 0): 128.0 * 2109100381,
+    ("backproject_cells_kernel", 0): 128.0 * 250832546,
     ("cells_to_coeffs_kernel", 0): 128.0 * 524288,
 }
 PEAK_L2_TBS = 8 * 16 * 128 * 2.4e9 / 1e12

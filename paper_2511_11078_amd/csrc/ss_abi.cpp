@@ -174,7 +174,7 @@ ss_status upload_geom(ss_ctx *ctx, const ss_geometry *g, hipStream_t st) {
     return fail(SS_EDEVICE, "geometry upload failed");
 }
 
-// Make the quadrature scratch (padded coefficients for the forward, the
+// Make the quadrature scratch (padded copies of the coefficients for the forward, the
 // knot-cell table for the adjoint) hold at least `need` floats.
 ss_status ensure_cells(ss_ctx *ctx, int64_t need) {
     if (need <= ctx->cells_cap) return SS_OK;

@@ -1,7 +1,7 @@
 // ss_kernels.hip -- gfx950 kernels of the spline x-ray transform.
 //
-//   pad_volume_kernel + project_kernel
-//                       forward model, one line per lane (quadrature form)
+//   pad_volume_zfast_kernel, pad_volume_kernel + project_kernel
+//                       forward model, one line per lane or per four lanes (quadrature form)
 //   backproject_cells_kernel + cells_to_coeffs_kernel
 //                       transpose: knot-cell gather, then coefficient gather (atomic-free)
 //   footprint_kernel    P phi(w, x) for arbitrary pairs (diagnostics)
@@ -424,7 +424,7 @@ __global__ void __launch_bounds__(256, n == 3 ? 3 : 4) project_kernel(const floa
 //
 // Pass 1 blocks own GX x GY x GZ bricks of cells and take the views in
 // batches: as many consecutive views as fit half of the LDS line table (a
-// few hundred lines, up to BATCH_VIEWS views; a view whose shadow is larger
+// few hundred lines, up to 8 views; a view whose shadow is larger
 // than that is taken alone, in segments).  Per batch the block
 //   - fills the half with the lines of each view's pixel rectangle (FP64
 //     set-up, anchor re-based at the brick centre), all threads taking part
@@ -450,7 +450,9 @@ __global__ void __launch_bounds__(256, n == 3 ? 3 : 4) project_kernel(const floa
 // partly filled line set-up per view instead of per batch, and a queue of
 // single entries, cone_256 took 187.5 ms at degree 3 and 70.9 ms at degree 0;
 // with the batches 156 and 50.6 ms (1.43e11 -> 1.32e11 and 3.79e10 -> 2.75e10
-// VALU instructions, half the scalar ones), and bit for bit the same sums.
+// VALU instructions, half the scalar ones), and with the plain slab test for
+// tables without axis-parallel lines 153 and 46.1 ms; bit for bit the same
+// sums.
 //
 // The cell table T holds (n+1)^3 FP32 entries per cell, entry-major
 // (T[a * cells + K], K x-fastest over the cells of a z-chunk), so that both
@@ -459,8 +461,6 @@ __global__ void __launch_bounds__(256, n == 3 ? 3 : 4) project_kernel(const floa
 // a chunk of L layers finalises L - n coefficient layers.
 // ---------------------------------------------------------------------------
 constexpr int GX = 8, GY = 8, GZ = 4;
-constexpr int BATCH_VIEWS = 8;        // views per batch: runs per thread and table half
-constexpr int RING = 2 * BATCH_VIEWS; // queued runs per thread
 constexpr int RUN_MAX = 64;           // columns and rows of a batched view's rectangle (6 bits each)
 constexpr int BV_CHUNK = 64;          // views whose brick constants are kept in LDS
 struct BrickViews {
@@ -472,18 +472,33 @@ struct BrickViews {
 // registers allow three waves per SIMD, so its table takes what LDS leaves
 // for three blocks per CU beside the queues, counting 160 KiB in 2 KiB
 // units; lower degrees fit four waves and a smaller table.
-template <int n> struct CellGather {
-    static constexpr int waves = n == 3 ? 3 : 4;          // waves per SIMD: blocks per CU
+// SHARED: blocks of 64 cells, a quarter (4 x 4 x 4) of a brick, whose (n+1)^3
+// moments are divided among n + 1 waves by the power of the third
+// coordinate; for launches of few bricks.  Anchors and cells stay relative to
+// the brick's centre and every moment is the same chain of FMAs, so the sums
+// are the same bit for bit.
+template <int n, bool SHARED> struct CellGather {
+    static constexpr int threads = SHARED ? 64 * (n + 1) : 256;
+    static constexpr int sx = SHARED ? 4 : GX, sy = SHARED ? 4 : GY;  // cells of a block (x GZ)
+    static constexpr int waves = n == 3 && !SHARED ? 3 : 4;  // waves per SIMD: blocks per CU
     static constexpr int lds = (160 * 1024 / waves) / 2048 * 2048;
-    static constexpr int fixed = RING * 256 * 4 + (int)sizeof(BrickViews) + 64;
-    static constexpr int half = std::min((lds - fixed) / 40 / 2 / 16 * 16, 480);  // lines per half (40 bytes each)
-    static constexpr int seg_cols = n == 3 ? 376 : 224;  // lines of a segment of a larger view
+    static constexpr int batch = SHARED ? 4 : 8;             // views per batch: runs per thread and table half
+    static constexpr int fixed = 2 * batch * threads * 4 + (int)sizeof(BrickViews) + 64;
+    static constexpr int half = SHARED ? 256 : std::min((lds - fixed) / 40 / 2 / 16 * 16, 480);  // lines per half (40 bytes each)
+    static constexpr int seg_cols = SHARED ? 256 : n == 3 ? 376 : 224;  // lines of a segment of a larger view
     // wave priority while a block sets up a batch (0: the default throughout)
     static constexpr int setup_prio = n == 0 ? 0 : 2;
     static_assert(2 * half <= 1024, "a run's first entry has 10 bits");
     static_assert(seg_cols <= half, "a segment fits a half");
 };
+// Launches of up to this many bricks, one per CU, share each cell's moments
+// (SHARED) at degrees 2 and 3: 32 views, degree 3, 225 bricks 164 -> 110 us,
+// 396 bricks 176 and 170, 637 bricks 208 and 234; degree 2, 225 bricks
+// 79 -> 72; degree 1 gains nothing (69 and 71).
+constexpr int SHARED_BRICKS = 256;
 constexpr float PIX_MARGIN = 1.0e-3f;           // pixels; covers FP32 rounding of the shadow bounds
+
+typedef float f32x2 __attribute__((ext_vector_type(2)));
 
 struct __attribute__((aligned(8))) CellRay {  // 40 bytes
     float a[3];      // point of the line nearest the brick centre, relative to it
@@ -492,7 +507,8 @@ struct __attribute__((aligned(8))) CellRay {  // 40 bytes
     float y;         // sinogram value
 };
 
-__device__ __forceinline__ void fill_cellray(CellRay &rec, const float *__restrict__ e, int kind, int R, int C, int j,
+// Returns whether the line is parallel to an axis.
+__device__ __forceinline__ bool fill_cellray(CellRay &rec, const float *__restrict__ e, int kind, int R, int C, int j,
                                              int i, const double centre[3], float yval) {
     const LineD L = make_line(e, kind, R, C, j, i, centre);
 #pragma unroll
@@ -504,16 +520,31 @@ __device__ __forceinline__ void fill_cellray(CellRay &rec, const float *__restri
         rec.iw[k] = wk != 0.0f ? __builtin_amdgcn_rcpf(wk) : 0.0f;
     }
     rec.y = L.ok ? yval : 0.0f;
+    return rec.iw[0] == 0.0f || rec.iw[1] == 0.0f || rec.iw[2] == 0.0f;
 }
 
 // Chord [t0, t1] of a line through the cell [lo, lo + 1]^3 (coordinates
 // relative to the brick centre).  A line parallel to a knot plane belongs to
 // the cell above it when it lies in the plane (the forward walk's choice);
 // for degree 0 the support is open and such a line meets neither cell.
-// Written without branches (selects only), so that the record is read in
-// one go and the lanes of a wave never split on the rare parallel axis.
+// Written without branches (selects only), so that the lanes of a wave never
+// split on a parallel axis.  `flat` (uniform): whether any line of the table
+// has one; without, the plain slab test gives the same values in 26 instead
+// of 50 instructions.
 template <int n>
-__device__ __forceinline__ bool cell_chord(const CellRay &r, const float lo[3], float &t0, float &t1) {
+__device__ __forceinline__ bool cell_chord(const CellRay &r, const float lo[3], bool flat, float &t0, float &t1) {
+    if (!flat) {
+        float a[3], b[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const float ta = (lo[k] - r.a[k]) * r.iw[k], tb = (lo[k] + 1.0f - r.a[k]) * r.iw[k];
+            a[k] = fminf(ta, tb);
+            b[k] = fmaxf(ta, tb);
+        }
+        t0 = fmaxf(fmaxf(a[0], a[1]), a[2]);
+        t1 = fminf(fminf(b[0], b[1]), b[2]);
+        return t0 < t1;
+    }
     bool in = true;
     t0 = -3.0e38f;
     t1 = 3.0e38f;
@@ -532,12 +563,13 @@ __device__ __forceinline__ bool cell_chord(const CellRay &r, const float lo[3], 
 // Add one line's chord through the cell to the cell's moments: at the m
 // Gauss-Legendre nodes of the chord, y * weight * u1^p1 u2^p2 u3^p3 for the
 // centred cell coordinates u = t - 1/2.
-template <int n>
-__device__ __forceinline__ void integrate_hit(const CellRay &r, const float lo[3], float acc[]) {
+// SHARED: only the moments of u3^q3 (q3 uniform), acc[p2 * (n+1) + p1].
+template <int n, bool SHARED>
+__device__ __forceinline__ void integrate_hit(const CellRay &r, const float lo[3], bool flat, int q3, float acc[]) {
     using Rule = GLRule<Degree<n>::m>;
     constexpr int NB = n + 1;
     float t0, t1;
-    if (!cell_chord<n>(r, lo, t0, t1)) return;  // a candidate whose line misses the cell
+    if (!cell_chord<n>(r, lo, flat, t0, t1)) return;  // a candidate whose line misses the cell
     const float mid = 0.5f * (t0 + t1), half = 0.5f * (t1 - t0);
     float uc[3], du[3];  // centred cell coordinate at mid, and its step
 #pragma unroll
@@ -554,12 +586,34 @@ __device__ __forceinline__ void integrate_hit(const CellRay &r, const float lo[3
         P1[0] = Rule::w(l) * sc;  // axis 1 carries the quadrature weight
         P2[0] = 1.0f;
         P3[0] = 1.0f;
-        const float u1 = fmaf(du[0], xi, uc[0]), u2 = fmaf(du[1], xi, uc[1]), u3 = fmaf(du[2], xi, uc[2]);
+        const float u1 = xi == 0.0f ? uc[0] : fmaf(du[0], xi, uc[0]), u2 = xi == 0.0f ? uc[1] : fmaf(du[1], xi, uc[1]),
+                    u3 = xi == 0.0f ? uc[2] : fmaf(du[2], xi, uc[2]);
 #pragma unroll
         for (int p = 1; p <= n; ++p) {
             P1[p] = P1[p - 1] * u1;
             P2[p] = p == 1 ? u2 : P2[p - 1] * u2;
             P3[p] = p == 1 ? u3 : P3[p - 1] * u3;
+        }
+        if constexpr (SHARED) {
+            // u3^q3 through the same products (factors of 1 are exact)
+            const float t3 = (q3 >= 2 ? u3 * u3 : 1.0f) * ((q3 & 1) ? u3 : 1.0f);
+            if (q3 == 0) {
+                // the last product of each power fused with its sum, as
+                // a + P1[p1] is below
+                acc[0] = fmaf(Rule::w(l), sc, acc[0]);
+#pragma unroll
+                for (int p1 = 1; p1 < NB; ++p1) acc[p1] = fmaf(P1[p1 - 1], u1, acc[p1]);
+            } else {
+#pragma unroll
+                for (int p1 = 0; p1 < NB; ++p1) acc[p1] = fmaf(t3, P1[p1], acc[p1]);
+            }
+#pragma unroll
+            for (int p2 = 1; p2 < NB; ++p2) {
+                const float z = t3 * P2[p2];
+#pragma unroll
+                for (int p1 = 0; p1 < NB; ++p1) acc[p2 * NB + p1] = fmaf(z, P1[p1], acc[p2 * NB + p1]);
+            }
+            continue;
         }
 #pragma unroll
         for (int p3 = 0; p3 < NB; ++p3)
@@ -596,8 +650,9 @@ __device__ __forceinline__ void pixel_rect(float cmin, float cmax, float rmin, f
 // pixel rectangle from its eight projected corners, and the shadow
 // half-widths F of its cells.  A corner on or behind the source plane has no
 // bounded shadow: the whole detector, and unbounded F.
-__device__ __forceinline__ void brick_view(const ViewProj &P, const double centre[3], int R, int C, BrickViews &B,
-                                           int s) {
+// The cells are [x0, x0 + sx] x [y0, y0 + sy] of the brick's GX x GY (all of GZ).
+__device__ __forceinline__ void brick_view(const ViewProj &P, const double centre[3], int x0, int sx, int y0, int sy,
+                                           int R, int C, BrickViews &B, int s) {
     const float oc = 0.5f * (float)(C - 1) + P.gac_f, orow = 0.5f * (float)(R - 1) + P.gar_f;
     const double *c = centre;
     const float nc = (float)(fma(c[2], P.du_s[2], fma(c[1], P.du_s[1], c[0] * P.du_s[0])) - P.odu);
@@ -608,7 +663,7 @@ __device__ __forceinline__ void brick_view(const ViewProj &P, const double centr
     float gmin = 3.0e38f, gmax = -3.0e38f, hmin = 3.0e38f, hmax = -3.0e38f;
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
-        const float d[3] = {(k & 1) ? 0.5f * GX : -0.5f * GX, (k & 2) ? 0.5f * GY : -0.5f * GY,
+        const float d[3] = {(float)(x0 + ((k & 1) ? sx : 0)) - 0.5f * GX, (float)(y0 + ((k & 2) ? sy : 0)) - 0.5f * GY,
                             (k & 4) ? 0.5f * GZ : -0.5f * GZ};
         const float den = fmaf(d[2], P.nmp_f[2], fmaf(d[1], P.nmp_f[1], fmaf(d[0], P.nmp_f[0], dn)));
         bad = bad || !(den > 0.0f);
@@ -642,22 +697,26 @@ __device__ __forceinline__ void brick_view(const ViewProj &P, const double centr
 // Three (degree 3, at most 168 VGPRs) or four (lower degrees, 128) waves per
 // SIMD keep as many blocks on a CU, to hide a batch's set-up between its
 // barriers behind other blocks' integration.
-template <int n>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CellGather<n>::waves)))
+template <int n, bool SHARED>
+__global__ void __launch_bounds__((CellGather<n, SHARED>::threads))
+__attribute__((amdgpu_waves_per_eu((CellGather<n, SHARED>::waves))))
 backproject_cells_kernel(const float *__restrict__ y, int N0, int N1, int N2, const float *__restrict__ geom,
                          const ViewProj *__restrict__ vps, int kind, int V, int R, int C, int mz0, int L,
                          float *__restrict__ T) {
     constexpr int NB = n + 1;
     constexpr int qoff = CellBasis<n>::qoff;
     constexpr double kap = (double)Degree<n>::kap;
-    constexpr int HALF = CellGather<n>::half, SEG_COLS = CellGather<n>::seg_cols;
+    constexpr int THREADS = CellGather<n, SHARED>::threads, SX = CellGather<n, SHARED>::sx, SY = CellGather<n, SHARED>::sy;
+    constexpr int BATCH_VIEWS = CellGather<n, SHARED>::batch, RING = 2 * BATCH_VIEWS;  // queued runs per thread
+    constexpr int MOMENTS = SHARED ? NB * NB : NB * NB * NB;  // of a thread
+    constexpr int HALF = CellGather<n, SHARED>::half, SEG_COLS = CellGather<n, SHARED>::seg_cols;
     // A batch's set-up (records, line table, queueing) is short dependent
     // chains ending in a barrier; the integration is long runs of
     // independent FMAs.  Raising a wave's priority for the set-up lets each
     // block reach its barrier sooner while the other blocks on the CU keep
     // the FMA pipes busy (degrees 1-3; the degree-0 kernel, whose
     // integration is short, runs faster without).
-    constexpr int PRIO = CellGather<n>::setup_prio;
+    constexpr int PRIO = CellGather<n, SHARED>::setup_prio;
     const auto prio_setup = [] {
         if constexpr (PRIO > 0) __builtin_amdgcn_s_setprio(PRIO);
     };
@@ -666,17 +725,22 @@ backproject_cells_kernel(const float *__restrict__ y, int N0, int N1, int N2, co
     };
     static_assert(sizeof(CellRay) == 40, "line record size assumed by the LDS budget");
     __shared__ CellRay rays[2 * HALF];
-    __shared__ uint32_t ring[RING * 256];  // per-thread queue of runs
+    __shared__ uint32_t ring[RING * THREADS];  // per-thread queue of runs
     __shared__ BrickViews bv;
+    __shared__ int flat_batch[2];  // last batch with a line parallel to an axis, per half
     const int M0 = N0 + n, M1 = N1 + n;  // cells per row / column
     const int nbx = (M0 + GX - 1) / GX, nby = (M1 + GY - 1) / GY, nbz = (L + GZ - 1) / GZ;
     const int nbricks = nbx * nby * nbz;
-    const int b = xcd_remap(blockIdx.x, nbricks);
+    const int part = SHARED ? blockIdx.x & 3 : 0;  // quarter of the brick
+    const int b = SHARED ? blockIdx.x >> 2 : xcd_remap(blockIdx.x, nbricks);
     const int bx = b % nbx, by = (b / nbx) % nby, bz = b / (nbx * nby);
     const int tid = threadIdx.x, lane = tid & 63;
-    const int tx = tid % GX, ty = (tid / GX) % GY, tz = tid / (GX * GY);
+    const int ox = (part & 1) * SX, oy = (part >> 1) * SY;
+    const int cell = SHARED ? lane : tid, q3 = SHARED ? tid >> 6 : 0;  // q3: the wave's power of u3
+    const int tx = ox + cell % SX, ty = oy + (cell / SX) % SY, tz = cell / (SX * SY);
     const int c0 = bx * GX + tx, c1 = by * GY + ty, c2 = bz * GZ + tz;  // cell, chunk-relative
     const bool mine = c0 < M0 && c1 < M1 && c2 < L;
+    if (SHARED && (bx * GX + ox >= M0 || by * GY + oy >= M1)) return;  // a quarter outside the volume
     // first cell of the brick in index units (cell K spans [K + kap, K + kap + 1]
     // in coordinates x + (N - 1)/2), and the brick centre in world coordinates
     const int mlo = -qoff - n;
@@ -686,9 +750,9 @@ backproject_cells_kernel(const float *__restrict__ y, int N0, int N1, int N2, co
     // this cell's low corner relative to the brick centre (exact)
     const float lo[3] = {(float)tx - 0.5f * GX, (float)ty - 0.5f * GY, (float)tz - 0.5f * GZ};
     const float oc = 0.5f * (float)(C - 1), orow = 0.5f * (float)(R - 1);
-    float acc[NB * NB * NB];
+    float acc[MOMENTS];
 #pragma unroll
-    for (int e = 0; e < NB * NB * NB; ++e) acc[e] = 0.0f;
+    for (int e = 0; e < MOMENTS; ++e) acc[e] = 0.0f;
 
     // This thread's queue: a ring of runs, oldest first, the next one to
     // start in slot qhead; the run being consumed is in registers (next
@@ -696,12 +760,13 @@ backproject_cells_kernel(const float *__restrict__ y, int N0, int N1, int N2, co
     // oldest `nolder` of them in the half that is not being filled.
     int qhead = 0, qtail = 0, count = 0, nolder = 0;
     int ent = 0, cleft = 0, rleft = 0, cols = 0, jump = 0;
+    bool flat = false, flat_other = false;  // such a line in either half, in the half filled last
     // integrate up to `rounds` of this thread's oldest entries
     auto drain = [&](int rounds) {
         const int npop = min(rounds, count);
         for (int k = 0; k < npop; ++k) {
             if (rleft == 0) {  // start the next run
-                const uint32_t d = ring[(qhead & (RING - 1)) * 256 + tid];
+                const uint32_t d = ring[(qhead & (RING - 1)) * THREADS + tid];
                 ++qhead;
                 ent = (int)(d & 1023u);
                 cols = (int)((d >> 10) & 63u) + 1;
@@ -715,7 +780,7 @@ backproject_cells_kernel(const float *__restrict__ y, int N0, int N1, int N2, co
             ent += wrap ? jump + 1 : 1;
             cleft = wrap ? cols : cleft;
             rleft -= wrap ? 1 : 0;
-            integrate_hit<n>(rays[cur], lo, acc);
+            integrate_hit<n, SHARED>(rays[cur], lo, flat, q3, acc);
         }
         count -= npop;
         nolder = max(nolder - npop, 0);
@@ -729,6 +794,7 @@ backproject_cells_kernel(const float *__restrict__ y, int N0, int N1, int N2, co
     // block-uniform: batch number, next view, first column and row of its
     // next segment (a larger view), views whose records are in LDS
     int batch = 0, v = 0, si = 0, sj = 0, rec0 = 0, rec1 = 0;
+    if (tid < 2) flat_batch[tid] = -1;
     while (true) {
         prio_setup();
         if (v + BATCH_VIEWS > rec1 && rec1 < V) {
@@ -736,7 +802,7 @@ backproject_cells_kernel(const float *__restrict__ y, int N0, int N1, int N2, co
             // old ones: they precede the last barrier)
             rec0 = v;
             rec1 = min(v + BV_CHUNK, V);
-            if (tid < rec1 - rec0) brick_view(vps[rec0 + tid], centre, R, C, bv, tid);
+            if (tid < rec1 - rec0) brick_view(vps[rec0 + tid], centre, ox, SX, oy, SY, R, C, bv, tid);
             __syncthreads();
         }
         // lane l < BATCH_VIEWS holds view v + l: its pixel rectangle, and the
@@ -765,7 +831,6 @@ backproject_cells_kernel(const float *__restrict__ y, int N0, int N1, int N2, co
         if (batch >= 2) __syncthreads();
         prio_setup();
         const int half = (batch & 1) * HALF;
-        ++batch;
         nolder = count;  // every queued entry is now in the older half
         int tb = upto - own, lines;
         const int vb = v;
@@ -792,7 +857,7 @@ backproject_cells_kernel(const float *__restrict__ y, int N0, int N1, int N2, co
             lines = __builtin_amdgcn_readlane(upto, K - 1);
             v += K;
         }
-        for (int base = 0; base < lines; base += 256) {
+        for (int base = 0; base < lines; base += THREADS) {
             const int t = base + tid;
             int idx = 0;  // the view of line t
             for (int k = 1; k < K; ++k) idx += t >= __builtin_amdgcn_readlane(tb, k) ? 1 : 0;
@@ -802,8 +867,9 @@ backproject_cells_kernel(const float *__restrict__ y, int N0, int N1, int N2, co
                 // least 1/(2b) away from an integer, far more than its rounding
                 const int q = (int)(((float)tt + 0.5f) * __builtin_amdgcn_rcpf((float)w));
                 const int jj = tj + q, ii = ti + (tt - q * w), vv = vb + idx;
-                fill_cellray(rays[half + t], geom + 12 * vv, kind, R, C, jj, ii, centre,
-                             y[((int64_t)vv * R + jj) * C + ii]);
+                if (fill_cellray(rays[half + t], geom + 12 * vv, kind, R, C, jj, ii, centre,
+                                 y[((int64_t)vv * R + jj) * C + ii]))
+                    flat_batch[batch & 1] = batch;
             }
         }
         for (int k = 0; k < K; ++k) {
@@ -833,7 +899,7 @@ backproject_cells_kernel(const float *__restrict__ y, int N0, int N1, int N2, co
                     rleft = nj + 1;
                     jump = w - cols;
                 } else {
-                    ring[(qtail & (RING - 1)) * 256 + tid] =
+                    ring[(qtail & (RING - 1)) * THREADS + tid] =
                         (uint32_t)first | (uint32_t)ni << 10 | (uint32_t)nj << 16 | (uint32_t)(w - 1) << 22;
                     ++qtail;
                 }
@@ -841,11 +907,15 @@ backproject_cells_kernel(const float *__restrict__ y, int N0, int N1, int N2, co
             }
         }
         __syncthreads();  // the half is filled; every record of this batch has been read
+        const bool now = flat_batch[batch & 1] == batch;
+        flat = now || flat_other;
+        flat_other = now;
+        ++batch;
     }
     // moments -> per-basis integrals: apply the blending map along each axis
     if constexpr (n > 0) {
 #pragma unroll
-        for (int i = 0; i < NB * NB; ++i) {  // axis 1: index (i, p1)
+        for (int i = 0; i < MOMENTS / NB; ++i) {  // axis 1: index (i, p1)
             float t[NB];
 #pragma unroll
             for (int a = 0; a < NB; ++a) {
@@ -857,7 +927,7 @@ backproject_cells_kernel(const float *__restrict__ y, int N0, int N1, int N2, co
             for (int a = 0; a < NB; ++a) acc[i * NB + a] = t[a];
         }
 #pragma unroll
-        for (int i3 = 0; i3 < NB; ++i3)  // axis 2: index (i3, p2, a1)
+        for (int i3 = 0; i3 < MOMENTS / (NB * NB); ++i3)  // axis 2: index (i3, p2, a1)
 #pragma unroll
             for (int i1 = 0; i1 < NB; ++i1) {
                 float t[NB];
@@ -870,6 +940,27 @@ backproject_cells_kernel(const float *__restrict__ y, int N0, int N1, int N2, co
 #pragma unroll
                 for (int a = 0; a < NB; ++a) acc[(i3 * NB + a) * NB + i1] = t[a];
             }
+        if constexpr (SHARED) {  // axis 3: the waves' moments through the line table's memory
+            static_assert(sizeof rays >= NB * NB * NB * 64 * 4, "room for a block's moments");
+            float *x = reinterpret_cast<float *>(rays);
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < NB * NB; ++i) x[(q3 * NB * NB + i) * 64 + lane] = acc[i];
+            __syncthreads();
+            float w[NB];
+#pragma unroll
+            for (int p = 0; p < NB; ++p) {
+                w[p] = blend_u<n>(0, p);
+#pragma unroll
+                for (int a = 1; a < NB; ++a) w[p] = q3 == a ? blend_u<n>(a, p) : w[p];
+            }
+#pragma unroll
+            for (int i = 0; i < NB * NB; ++i) {
+                acc[i] = 0.0f;
+#pragma unroll
+                for (int p = 0; p < NB; ++p) acc[i] = fmaf(w[p], x[(p * NB * NB + i) * 64 + lane], acc[i]);
+            }
+        } else
 #pragma unroll
         for (int i = 0; i < NB * NB; ++i) {  // axis 3: index (p3, i)
             float t[NB];
@@ -887,7 +978,7 @@ backproject_cells_kernel(const float *__restrict__ y, int N0, int N1, int N2, co
         const int64_t cells = (int64_t)M0 * M1 * L;
         const int64_t K = ((int64_t)c2 * M1 + c1) * M0 + c0;
 #pragma unroll
-        for (int a = 0; a < NB * NB * NB; ++a) T[a * cells + K] = acc[a];
+        for (int a = 0; a < MOMENTS; ++a) T[(q3 * MOMENTS + a) * cells + K] = acc[a];
     }
 }
 
@@ -1080,8 +1171,18 @@ static hipError_t launch_backproject_n(const LaunchArgs &a, hipStream_t st) {
     for (int s = mlo;;) {
         const int L = std::min(Lmax, mlo + M2 - s);
         const int nb = ((M0 + GX - 1) / GX) * ((M1 + GY - 1) / GY) * ((L + GZ - 1) / GZ);
-        hipLaunchKernelGGL(backproject_cells_kernel<n>, dim3(nb), dim3(256), 0, st, a.sino_in, a.N[0], a.N[1],
-                           a.N[2], a.geom, a.vproj, a.kind, a.V, a.R, a.C, s, L, a.scratch);
+        const auto gather = [&](auto shared) {
+            constexpr bool SHARED = decltype(shared)::value;
+            hipLaunchKernelGGL((backproject_cells_kernel<n, SHARED>), dim3(SHARED ? 4 * nb : nb),
+                               dim3(CellGather<n, SHARED>::threads), 0, st, a.sino_in, a.N[0], a.N[1], a.N[2], a.geom,
+                               a.vproj, a.kind, a.V, a.R, a.C, s, L, a.scratch);
+        };
+        if constexpr (n >= 2) {
+            if (nb <= SHARED_BRICKS) gather(std::true_type{});
+            else gather(std::false_type{});
+        } else {
+            gather(std::false_type{});
+        }
         const int qz0 = s + qoff + n, qz1 = std::min(s + L - 1 + qoff, a.N[2] - 1);
         if (qz1 >= qz0) {
             const int64_t cnt = plane * (qz1 - qz0 + 1);

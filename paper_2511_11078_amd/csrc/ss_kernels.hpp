@@ -55,7 +55,8 @@ int project_quad_copies(int degree, const int N[3]);
 hipError_t launch_project_quad(int degree, const LaunchArgs &a, hipStream_t st);
 
 // Static scratch of the allocation-free forward (ss_project_noalloc): view
-// vectors, then the zero-padded coefficients, in one file-scope device array
+// vectors, then one zero-padded copy of the coefficients at a time (two where
+// they fit), in one file-scope device array
 // of STATIC_SCRATCH_FLOATS floats per GPU.  static_scratch_address returns
 // its device address on `device`, which must be the current device (looked
 // up once per device, then cached).

@@ -2,8 +2,10 @@
 
 A block takes its views in batches: up to 8 consecutive views whose line
 rectangles together fit half of its line table, a larger view alone in
-segments, per-view constants for 64 views at a time.  The cases sit on the
-edges of those rules; the bar is the quadrature form's (relative L2 1e-5 for
+segments, per-view constants for 64 views at a time; a table with an
+axis-parallel line takes another slab test; at degrees 2 and 3 volumes of up
+to 256 bricks share each cell's moments among waves, of larger ones a thread
+holds them all.  The cases sit on the edges of those rules; the bar is the quadrature form's (relative L2 1e-5 for
 FP32 arithmetic, 1e-4 for degree 0, whose outputs jump where a line runs
 within rounding of a voxel face).
 """
@@ -41,21 +43,46 @@ CASES = {
     "batches_and_segments_in_turn": (22, 60, 90, [1.0, 0.62, 0.5, 0.2], 0.0),
     "wider_than_a_run": (5, 4, 300, [0.11], 0.0),
 }
+VOLUMES = {"small": (11, 9, 6), "large": (61, 53, 25)}  # 12 and 392 bricks of cells at degree 3
+
+
+def _adjoint_error(n, geom, dims, seed):
+    y = np.random.default_rng(seed).standard_normal((geom.n_views, geom.det_rows, geom.det_cols)).astype(np.float32)
+    ctx = Context(n, "quad", 0)
+    got = to_np(ctx.backproject(to_gpu(y), geom, dims))
+    ctx.close()
+    coefs = synth.sample_indices(int(np.prod(dims)), 600, seed=seed + 1)
+    want = oracle.backproject_subset(y, geom, dims, n, coefs=coefs)
+    assert np.abs(want).max() > 0
+    return rel_l2(got.ravel()[coefs], want)
 
 
 @pytest.mark.parametrize("n", [0, 1, 2, 3])
 @pytest.mark.parametrize("case", list(CASES))
-def test_view_batches(n, case):
-    say(f"cell gather {case} n={n}")
+@pytest.mark.parametrize("volume", list(VOLUMES))
+def test_view_batches(n, case, volume):
+    say(f"cell gather {case} {volume} n={n}")
     views, R, C, pitches, shift = CASES[case]
-    dims = (11, 9, 6)
+    if volume == "large":  # as many pixels per cell, over more of the volume
+        R, C = max(R, 24), max(C, 33)
     geom = synth.Geometry("parallel", views, R, C, _tilted(views, pitches, shift, seed=300 + n))
-    y = np.random.default_rng(310 + n).standard_normal((views, R, C)).astype(np.float32)
-    ctx = Context(n, "quad", 0)
-    got = to_np(ctx.backproject(to_gpu(y), geom, dims))
-    ctx.close()
-    want = oracle.backproject_subset(y, geom, dims, n)
-    e = rel_l2(got, want)
+    e = _adjoint_error(n, geom, VOLUMES[volume], 310 + n)
     say(f"  rel-L2 {e:.3e}")
-    assert np.abs(want).max() > 0
+    assert e <= (1e-5 if n > 0 else 1e-4)
+
+
+@pytest.mark.parametrize("n", [0, 1, 2, 3])
+@pytest.mark.parametrize("volume", list(VOLUMES))
+def test_axis_parallel_lines_in_some_batches(n, volume):
+    """Groups of views whose lines all, some or none run parallel to an axis,
+    in and beside the knot planes."""
+    say(f"cell gather axis-parallel lines {volume} n={n}")
+    dirs = list(synth.great_circle_plus_tilts(7, 9, seed=320)) + [[1, 0, 0], [0, 1, 0], [0, 0, 1]]
+    dirs += list(synth.uniform_directions(11, seed=321)) + [[0, 0.6, 0.8], [0.6, 0, 0.8]]
+    geom = synth.parallel_geometry(np.asarray(dirs, dtype=np.float64), 23, 26)
+    # off the voxel faces at degree 0, where a line in a face meets no voxel
+    if n == 0:
+        geom.vecs[:, 3:6] += np.float32(0.17)
+    e = _adjoint_error(n, geom, VOLUMES[volume], 330 + n)
+    say(f"  rel-L2 {e:.3e}")
     assert e <= (1e-5 if n > 0 else 1e-4)
