@@ -67,19 +67,19 @@ MLP_TRANS_PER_PAIR = 2 * 4 * 64   # SiLU of 4 x 64 hidden units: one exp and one
 # profiles/cone256_traffic_counters.md.  Valid only for the kernel sources they
 # were measured on (SHA-256 over QUAD_SOURCES); otherwise reported as null.
 QUAD_SOURCES = ["csrc/ss_kernels.hip", "csrc/ss_math.hpp", "csrc/ss_traverse.hpp", "csrc/ss_kernels.hpp"]
-TRAFFIC_SHA256 = "055f8d65d185177885dc6de4f2fb0bc6bc7ceeb1415beaf6fdd59f6bc417fd1e"
+TRAFFIC_SHA256 = "1151696d092da40c8130e7e1c1bb9c7bf3e1f61ab7b5c292de244182e0b79f5a"
 TRAFFIC_BYTES = {  # (kernel, degree) -> (read bytes, written bytes) per application, cone_256
-    ("pad_volume_kernel", 3): (2.0 * 36889 * 1024, 1.0 * 71874 * 1024),
-    ("pad_volume_zfast_kernel", 3): (2.0 * 65558 * 1024, 1.0 * 72249 * 1024),
+    ("pad_volume_kernel", 3): (2.0 * 36888 * 1024, 1.0 * 71874 * 1024),
+    ("pad_volume_zfast_kernel", 3): (2.0 * 65558 * 1024, 1.0 * 72265 * 1024),
     ("pad_volume_yfast_kernel", 3): (0.0, 0.0),  # a y-fastest copy is no longer made
-    ("project_kernel", 3): (2.0 * 3801500 * 1024, 1.0 * 255417 * 1024),
-    ("backproject_cells_kernel", 3): (2.0 * 3018088 * 1024, 1.0 * 5623803 * 1024),
-    ("cells_to_coeffs_kernel", 3): (2.0 * 2449364 * 1024, 1.0 * 65536 * 1024),
-    ("pad_volume_zfast_kernel", 0): (2.0 * 65561 * 1024, 1.0 * 80217 * 1024),
+    ("project_kernel", 3): (2.0 * 3799960 * 1024, 1.0 * 231493 * 1024),
+    ("backproject_cells_kernel", 3): (2.0 * 3017691 * 1024, 1.0 * 5625953 * 1024),
+    ("cells_to_coeffs_kernel", 3): (2.0 * 2488769 * 1024, 1.0 * 65536 * 1024),
+    ("pad_volume_zfast_kernel", 0): (2.0 * 65561 * 1024, 1.0 * 80242 * 1024),
     ("pad_volume_kernel", 0): (2.0 * 36888 * 1024, 1.0 * 67084 * 1024),
-    ("project_kernel", 0): (2.0 * 2965582 * 1024, 1.0 * 267903 * 1024),
-    ("backproject_cells_kernel", 0): (2.0 * 1240164 * 1024, 1.0 * 67567 * 1024),
-    ("cells_to_coeffs_kernel", 0): (2.0 * 32788 * 1024, 1.0 * 65536 * 1024),
+    ("project_kernel", 0): (2.0 * 2965332 * 1024, 1.0 * 267956 * 1024),
+    ("backproject_cells_kernel", 0): (2.0 * 1246372 * 1024, 1.0 * 67484 * 1024),
+    ("cells_to_coeffs_kernel", 0): (2.0 * 32787 * 1024, 1.0 * 65536 * 1024),
 }
 
 
@@ -92,13 +92,13 @@ L2_FILL_BYTES = {  # (kernel, degree) -> bytes per application, cone_256
     ("pad_volume_kernel", 3): 128.0 * 589824,
     ("pad_volume_zfast_kernel", 3): 128.0 * 1048576,
     ("pad_volume_yfast_kernel", 3): 0.0,
-    ("project_kernel", 3): 128.0 * 10405279318,
-    ("backproject_cells_kernel", 3): 128.0 * 270358594,
-    ("cells_to_coeffs_kernel", 3): 128.0 * 45512386,
+    ("project_kernel", 3): 128.0 * 11807933075,
+    ("backproject_cells_kernel", 3): 128.0 * 270371921,
+    ("cells_to_coeffs_kernel", 3): 128.0 * 45094432,
     ("pad_volume_zfast_kernel", 0): 128.0 * 1048576,
     ("pad_volume_kernel", 0): 128.0 * 589824,
-    ("project_kernel", 0): 128.0 * 2109100381,
-    ("backproject_cells_kernel", 0): 128.0 * 250832546,
+    ("project_kernel", 0): 128.0 * 2107719385,
+    ("backproject_cells_kernel", 0): 128.0 * 250832869,
     ("cells_to_coeffs_kernel", 0): 128.0 * 524288,
 }
 PEAK_L2_TBS = 8 * 16 * 128 * 2.4e9 / 1e12

@@ -111,6 +111,15 @@ __device__ __forceinline__ ViewWalk view_walk(const float *__restrict__ e, int k
 // Launches of up to this many 16 x 16-pixel tiles share each line among four
 // lanes (project_kernel).
 constexpr int64_t FWD_SHARED_TILES = 2048;
+// Copies of up to this many floats (128 MiB) are walked in waves of 8 x 8
+// pixels instead of 16 x 4 at degrees 2 and 3.  Square waves idle less where
+// lines leave the volume (16 x 4 against 8 x 8: 128^3 with 192^2 pixels
+// degree 3 12.5 and 11.5 ms, degree 2 5.6 and 5.2; 180 x 180 x 50 with 50 x
+// 180 pixels degree 2 3.9 and 3.6; 256^3 with 384^2 150.7 and 150.8);
+// long ones read fewer cache lines, which counts where the copy is large
+// (384^3 53.7 and 54.1, 512^3 127.4 and 128.9) or the integral short (cone_256
+// degree 1 29.4 and 30.3, degree 0 12.0 and 12.4).
+constexpr int64_t FWD_SQUARE_FLOATS = (int64_t)1 << 25;
 // Largest padded copy (floats, 1 GiB) that is kept in both orders, so that
 // one launch walks every view.
 constexpr int64_t FWD_BOTH_FLOATS = (int64_t)1 << 28;
@@ -216,8 +225,13 @@ __global__ void __launch_bounds__(256, n == 3 ? 3 : 4) project_kernel(const floa
     const int sub = lane & (LPL - 1);
     int j, i;
     if constexpr (LPL == 1) {
-        // a wave takes 16 x 4 pixels, consecutive lanes along the long side
-        const int along = lane & 15, across = wave * 4 + (lane >> 4);
+        // a wave takes 16 x 4 pixels, consecutive lanes along the long side,
+        // or 8 x 8 (FWD_SQUARE_FLOATS)
+        const bool square = n >= 2 && !WIDE &&
+                            (int64_t)(N0 + 2 * FWD_PAD(n)) * (N1 + 2 * FWD_PAD(n)) * (N2 + 2 * FWD_PAD(n)) <=
+                                FWD_SQUARE_FLOATS;
+        const int along = square ? (wave >> 1) * 8 + (lane & 7) : lane & 15;
+        const int across = square ? (wave & 1) * 8 + (lane >> 3) : wave * 4 + (lane >> 4);
         j = tr * 16 + (vw.rows ? along : across);
         i = tc_ * 16 + (vw.rows ? across : along);
     } else {

@@ -90,3 +90,19 @@ def test_copy_above_4_gib():
     e = rel_l2(got, want)
     say(f"  rel-L2 {e:.3e}")
     assert np.abs(want).max() > 0 and e <= 1e-5
+
+
+@pytest.mark.parametrize("n", [2, 3])
+@pytest.mark.parametrize("dims", [(310, 320, 310), (340, 330, 310)])
+def test_lane_tiles(n, dims):
+    """Copies just below and above 2^25 floats, walked in waves of 8 x 8 and
+    of 16 x 4 pixels: 2100 tiles in one launch, and 420 a launch (four lanes
+    a line).  No line's sum depends on its lane."""
+    say(f"lane tiles n={n} {dims}")
+    geom = synth.parallel_geometry(synth.uniform_directions(5, seed=430), 330, 310, pitch=1.3)
+    c = to_gpu(np.random.default_rng(431).standard_normal(dims[::-1]).astype(np.float32))
+    ctx = Context(n, "quad", 0)
+    whole = ctx.project(c, geom)
+    parts = [ctx.project(c, geom.subset_views(v, v + 1)) for v in range(5)]
+    assert torch.equal(whole, torch.cat(parts))
+    ctx.close()
