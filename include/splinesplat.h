@@ -129,7 +129,9 @@ ss_status ss_destroy(ss_ctx *ctx);
  * d_sino: FP32 [n_views][det_rows][det_cols], overwritten.
  * With SS_FORM_QUAD_FP32 the context's device scratch (the one described
  * at ss_backproject) first receives a zero-padded copy of d_coeffs,
- * (dims + 2 degree + 2) floats per axis.
+ * (dims + 2 degree + 2) floats per axis, and a second one in another order
+ * where both take up to 2 GiB, fit the scratch limit and can be allocated
+ * (otherwise the two share one place in turn; the result is the same).
  * Errors: SS_EINVAL (null pointers, dims < 1 or > 4096, non-finite vecs,
  * zero-length ray direction, more than 2^31 rays per call), SS_ENOMEM. */
 ss_status ss_project(ss_ctx *ctx, const float *d_coeffs, const int64_t dims[3],
@@ -138,9 +140,10 @@ ss_status ss_project(ss_ctx *ctx, const float *d_coeffs, const int64_t dims[3],
 /* Adjoint (exact transpose of ss_project up to FP32 rounding):
  * d_coeffs[k] = sum over lines m of d_sino[m] * P phi(w_m, s_m - Proj k),
  * overwritten.  Same layouts and errors as ss_project.
- * With SS_FORM_QUAD_FP32 the context keeps a device table of (degree+1)^3
- * floats per knot cell of the support-padded volume (4.45 GB for 256^3,
- * 35.6 GB for 512^3, degree 3), allocated on the first call that needs it
+ * With SS_FORM_QUAD_FP32 the context keeps a device table of the parts that
+ * 8 x 8 x 4 knot cells of the support-padded volume add to the coefficients
+ * around them (0.48 GB for 256^3, 3.7 GB for 512^3, degree 3; volumes of few
+ * cells, in 4 x 4 x 4), allocated on the first call that needs it
  * and at most the context's scratch limit (64 GiB unless set with
  * ss_set_scratch_limit; a larger table is processed in z-chunks of cell
  * layers, recomputing `degree` layers at each chunk boundary; the result

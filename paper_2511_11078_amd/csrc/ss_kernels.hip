@@ -429,12 +429,12 @@ __global__ void __launch_bounds__(256, n == 3 ? 3 : 4) project_kernel(const floa
 // gathers, over all views, the lines of the pixels whose centres fall in the
 // detector shadow of its cell, accumulates the centred moments of their
 // chords (integrate_hit) and at the end maps them to the (n+1)^3 per-basis
-// integrals (T[K][a] below, a = q - K - qoff per axis).  Pass 2 gives every
-// coefficient to one thread, which adds its (n+1)^3 entries T[q - qoff - a][a]
-// of the cells its support covers.  Every (line, basis) pair of eq. (4)
-// is evaluated through the same per-cell Gauss-Legendre terms as the
-// forward, each output has a single writer, and the summation order is
-// fixed.
+// integrals (entry a = q - K - qoff per axis of cell K), which the block sums
+// per coefficient over its cells.  Pass 2 gives every coefficient to one
+// thread, which adds its parts of the blocks that hold cells of its support.
+// Every (line, basis) pair of eq. (4) is evaluated through the same per-cell
+// Gauss-Legendre terms as the forward, each output has a single writer, and
+// the summation order is fixed.
 //
 // Pass 1 blocks own GX x GY x GZ bricks of cells and take the views in
 // batches: as many consecutive views as fit half of the LDS line table (a
@@ -468,11 +468,14 @@ __global__ void __launch_bounds__(256, n == 3 ? 3 : 4) project_kernel(const floa
 // tables without axis-parallel lines 153 and 46.1 ms; bit for bit the same
 // sums.
 //
-// The cell table T holds (n+1)^3 FP32 entries per cell, entry-major
-// (T[a * cells + K], K x-fastest over the cells of a z-chunk), so that both
-// passes access it coalesced.  Volumes whose table would exceed the
-// context's scratch are processed in overlapping z-chunks of cell layers:
-// a chunk of L layers finalises L - n coefficient layers.
+// The table between the passes holds, per block, the FP64 parts of the
+// coefficients whose support meets its cells (11 x 11 x 7 for 8 x 8 x 4 cells
+// at degree 3: 6.8 KB, where the entries of the cells themselves take 64 KB;
+// 512^3, 32 views of 768 x 768: 35.6 -> 3.7 GB of table, 134 -> 127 ms;
+// cone_256 4.5 -> 0.5 GB, 156.6 -> 155.1 ms; degrees 0 and 1 unchanged).
+// Volumes whose table would exceed the context's scratch are processed in
+// overlapping z-chunks of cell layers: a chunk of L layers finalises L - n
+// coefficient layers.
 // ---------------------------------------------------------------------------
 constexpr int GX = 8, GY = 8, GZ = 4;
 constexpr int RUN_MAX = 64;           // columns and rows of a batched view's rectangle (6 bits each)
@@ -499,6 +502,9 @@ template <int n, bool SHARED> struct CellGather {
     static constexpr int batch = SHARED ? 4 : 8;             // views per batch: runs per thread and table half
     static constexpr int fixed = 2 * batch * threads * 4 + (int)sizeof(BrickViews) + 64;
     static constexpr int half = SHARED ? 256 : std::min((lds - fixed) / 40 / 2 / 16 * 16, 480);  // lines per half (40 bytes each)
+    // coefficients whose support meets a block's cells, and that count made even
+    static constexpr int coeffs = (sx + n) * (sy + n) * (GZ + n), record = (coeffs + 1) / 2 * 2;
+    using Part = std::conditional_t<n == 0, float, double>;  // a coefficient's part (degree 0: one FP32 entry)
     static constexpr int seg_cols = SHARED ? 256 : n == 3 ? 376 : 224;  // lines of a segment of a larger view
     // wave priority while a block sets up a batch (0: the default throughout)
     static constexpr int setup_prio = n == 0 ? 0 : 2;
@@ -716,7 +722,7 @@ __global__ void __launch_bounds__((CellGather<n, SHARED>::threads))
 __attribute__((amdgpu_waves_per_eu((CellGather<n, SHARED>::waves))))
 backproject_cells_kernel(const float *__restrict__ y, int N0, int N1, int N2, const float *__restrict__ geom,
                          const ViewProj *__restrict__ vps, int kind, int V, int R, int C, int mz0, int L,
-                         float *__restrict__ T) {
+                         typename CellGather<n, SHARED>::Part *__restrict__ T) {
     constexpr int NB = n + 1;
     constexpr int qoff = CellBasis<n>::qoff;
     constexpr double kap = (double)Degree<n>::kap;
@@ -988,46 +994,70 @@ backproject_cells_kernel(const float *__restrict__ y, int N0, int N1, int N2, co
             for (int a = 0; a < NB; ++a) acc[a * NB * NB + i] = t[a];
         }
     }
-    if (mine) {
-        const int64_t cells = (int64_t)M0 * M1 * L;
-        const int64_t K = ((int64_t)c2 * M1 + c1) * M0 + c0;
+    // this block's part of each coefficient: its cells' entries summed in
+    // FP64, entry by entry, (n+1)^2 entries of every cell at a time through
+    // the line table's memory (all of them when the waves share the moments)
+    constexpr int NC = CellGather<n, SHARED>::coeffs, CELLS = SHARED ? 64 : 256;
+    constexpr int PER = (NC + THREADS - 1) / THREADS, EX = SX + n, EY = SY + n;
+    static_assert(sizeof rays >= (SHARED ? NB : 1) * NB * NB * CELLS * 4, "room for the entries");
+    float *x = reinterpret_cast<float *>(rays);
+    double sum[PER];
 #pragma unroll
-        for (int a = 0; a < MOMENTS; ++a) T[(q3 * MOMENTS + a) * cells + K] = acc[a];
+    for (int r = 0; r < PER; ++r) sum[r] = 0.0;
+#pragma unroll
+    for (int a3 = 0; a3 < NB; ++a3) {
+        if (!SHARED || a3 == 0) {
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < NB * NB; ++i)
+                x[((SHARED ? q3 * NB * NB : 0) + i) * CELLS + cell] = acc[SHARED ? i : a3 * NB * NB + i];
+            __syncthreads();
+        }
+#pragma unroll
+        for (int r = 0; r < PER; ++r) {
+            const int e = tid + r * THREADS, i = e % EX, j = (e / EX) % EY, z = e / (EX * EY) - a3;
+            if (e >= NC || z < 0 || z >= GZ) continue;
+            for (int a2 = 0; a2 < NB; ++a2) {
+                if (j - a2 < 0 || j - a2 >= SY) continue;
+                const float *row = x + ((SHARED ? a3 * NB * NB : 0) + a2 * NB) * CELLS + (z * SY + j - a2) * SX + i;
+#pragma unroll
+                for (int a1 = 0; a1 < NB; ++a1)
+                    if (i - a1 >= 0 && i - a1 < SX) sum[r] += (double)row[a1 * CELLS - a1];
+            }
+        }
     }
+    const int qx = SHARED ? 2 * bx + (part & 1) : bx, qy = SHARED ? 2 * by + (part >> 1) : by;
+    const int nqx = SHARED ? 2 * nbx : nbx, nqy = SHARED ? 2 * nby : nby;
+    auto *out = T + (((int64_t)bz * nqy + qy) * nqx + qx) * CellGather<n, SHARED>::record;
+#pragma unroll
+    for (int r = 0; r < PER; ++r)
+        if (tid + r * THREADS < NC) out[tid + r * THREADS] = (typename CellGather<n, SHARED>::Part)sum[r];
 }
 
-// Pass 2: coefficient q (layer q2 in [qz0, qz1]) adds T[K][a] over the cells
-// K = q - qoff - a of its support (FP64 sum of the (n+1)^3 FP32 entries).
-template <int n>
-__global__ void __launch_bounds__(256) cells_to_coeffs_kernel(const float *__restrict__ T, int N0, int N1,
-                                                              int mz0, int L, int qz0, int qz1,
+// Pass 2: coefficient k (layer k2 in [qz0, qz1]) adds its parts of the blocks
+// that hold cells of its support (up to two per axis), in FP64.
+template <int n, bool SHARED>
+__global__ void __launch_bounds__(256) cells_to_coeffs_kernel(const typename CellGather<n, SHARED>::Part *__restrict__ T,
+                                                              int N0, int N1, int mz0, int qz0, int qz1,
                                                               float *__restrict__ c) {
-    constexpr int NB = n + 1;
     constexpr int qoff = CellBasis<n>::qoff;
+    using G = CellGather<n, SHARED>;
     const int64_t per = (int64_t)N0 * N1;
     const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (idx >= per * (qz1 - qz0 + 1)) return;
     const int k2 = qz0 + (int)(idx / per);
     const int rem = (int)(idx % per);
     const int k1 = rem / N0, k0 = rem % N0;
-    const int M0 = N0 + n, M1 = N1 + n;
-    const int mlo = -qoff - n;
-    const int64_t cells = (int64_t)M0 * M1 * L;
+    const int nqx = (N0 + n + GX - 1) / GX * (GX / G::sx), nqy = (N1 + n + GY - 1) / GY * (GY / G::sy);
+    // cells of the support, relative to the volume's (the chunk's) first:
+    // k0 .. k0 + n, k1 .. k1 + n, z .. z + n
+    const int z = k2 - qoff - mz0 - n;
     double s = 0.0;
-#pragma unroll
-    for (int a3 = 0; a3 < NB; ++a3) {
-        const int z = k2 - qoff - a3 - mz0;  // in [0, L) for qz0 <= k2 <= qz1
-#pragma unroll
-        for (int a2 = 0; a2 < NB; ++a2) {
-            const int yy = k1 - qoff - a2 - mlo;
-#pragma unroll
-            for (int a1 = 0; a1 < NB; ++a1) {
-                const int xx = k0 - qoff - a1 - mlo;
-                const int64_t K = ((int64_t)z * M1 + yy) * M0 + xx;
-                s += (double)T[((a3 * NB + a2) * NB + a1) * cells + K];
-            }
-        }
-    }
+    for (int bz = z / GZ; bz <= (z + n) / GZ; ++bz)
+        for (int by = k1 / G::sy; by <= (k1 + n) / G::sy; ++by)
+            for (int bx = k0 / G::sx; bx <= (k0 + n) / G::sx; ++bx)
+                s += T[(((int64_t)bz * nqy + by) * nqx + bx) * G::record +
+                       ((z + n - bz * GZ) * (G::sy + n) + k1 + n - by * G::sy) * (G::sx + n) + k0 + n - bx * G::sx];
     c[(int64_t)k2 * per + rem] = (float)s;
 }
 
@@ -1162,51 +1192,67 @@ int project_quad_copies(int degree, const int N[3]) {
     return project_quad_scratch_floats(degree, N) <= FWD_BOTH_FLOATS ? 2 : 1;
 }
 
-int64_t backproject_quad_scratch_floats(int degree, const int N[3], int64_t limit) {
-    const int64_t nb = degree + 1;
-    const int64_t layer = nb * nb * nb * (int64_t)(N[0] + degree) * (N[1] + degree);
-    const int64_t full = layer * (N[2] + degree);
-    // at least 4 (n + 1) layers per chunk, so that chunking re-does at most
-    // a quarter of the cell layers
-    const int64_t floor_layers = std::min<int64_t>(N[2] + degree, 4 * nb);
-    return std::min(full, std::max(limit, layer * floor_layers));
+// Whether the adjoint of a volume shares each cell's moments, and the floats
+// of the table per GZ cell layers.
+template <int n> static bool cells_shared(const int N[3]) {
+    const int64_t nb = (int64_t)((N[0] + n + GX - 1) / GX) * ((N[1] + n + GY - 1) / GY) * ((N[2] + n + GZ - 1) / GZ);
+    return n >= 2 && nb <= SHARED_BRICKS;
+}
+template <int n> static int64_t cell_table_floats(const int N[3]) {
+    const int64_t bricks = (int64_t)((N[0] + n + GX - 1) / GX) * ((N[1] + n + GY - 1) / GY);
+    const int64_t record = cells_shared<n>(N) ? 4 * CellGather<n, true>::record : CellGather<n, false>::record;
+    return bricks * record * (int64_t)(sizeof(typename CellGather<n, false>::Part) / sizeof(float));
 }
 
-template <int n>
-static hipError_t launch_backproject_n(const LaunchArgs &a, hipStream_t st) {
+template <int n> static int64_t scratch_floats_n(const int N[3], int64_t limit) {
+    const int64_t slab = cell_table_floats<n>(N);
+    // at least 4 (n + 1) layers per chunk, so that chunking re-does at most
+    // a quarter of the cell layers
+    const int64_t floor_layers = std::min<int64_t>(N[2] + n, 4 * (n + 1));
+    return std::min(slab * ((N[2] + n + GZ - 1) / GZ), std::max(limit, slab * ((floor_layers + GZ - 1) / GZ)));
+}
+
+int64_t backproject_quad_scratch_floats(int degree, const int N[3], int64_t limit) {
+    switch (degree) {
+    case 0: return scratch_floats_n<0>(N, limit);
+    case 1: return scratch_floats_n<1>(N, limit);
+    case 2: return scratch_floats_n<2>(N, limit);
+    default: return scratch_floats_n<3>(N, limit);
+    }
+}
+
+template <int n, bool SHARED>
+static hipError_t launch_backproject_cells(const LaunchArgs &a, hipStream_t st) {
     constexpr int qoff = CellBasis<n>::qoff;
-    constexpr int64_t NB3 = (int64_t)(n + 1) * (n + 1) * (n + 1);
     const int M0 = a.N[0] + n, M1 = a.N[1] + n, M2 = a.N[2] + n;
-    const int64_t layer = NB3 * M0 * M1;
-    const int Lmax = (int)std::min<int64_t>(M2, a.scratch_floats / layer);
+    const int Lmax = (int)std::min<int64_t>(M2, a.scratch_floats / cell_table_floats<n>(a.N) * GZ);
     if (!a.scratch || Lmax <= n) return hipErrorInvalidValue;
+    auto *T = reinterpret_cast<typename CellGather<n, SHARED>::Part *>(a.scratch);
     const int mlo = -qoff - n;
     const int64_t plane = (int64_t)a.N[0] * a.N[1];
     for (int s = mlo;;) {
         const int L = std::min(Lmax, mlo + M2 - s);
         const int nb = ((M0 + GX - 1) / GX) * ((M1 + GY - 1) / GY) * ((L + GZ - 1) / GZ);
-        const auto gather = [&](auto shared) {
-            constexpr bool SHARED = decltype(shared)::value;
-            hipLaunchKernelGGL((backproject_cells_kernel<n, SHARED>), dim3(SHARED ? 4 * nb : nb),
-                               dim3(CellGather<n, SHARED>::threads), 0, st, a.sino_in, a.N[0], a.N[1], a.N[2], a.geom,
-                               a.vproj, a.kind, a.V, a.R, a.C, s, L, a.scratch);
-        };
-        if constexpr (n >= 2) {
-            if (nb <= SHARED_BRICKS) gather(std::true_type{});
-            else gather(std::false_type{});
-        } else {
-            gather(std::false_type{});
-        }
+        hipLaunchKernelGGL((backproject_cells_kernel<n, SHARED>), dim3(SHARED ? 4 * nb : nb),
+                           dim3(CellGather<n, SHARED>::threads), 0, st, a.sino_in, a.N[0], a.N[1], a.N[2], a.geom,
+                           a.vproj, a.kind, a.V, a.R, a.C, s, L, T);
         const int qz0 = s + qoff + n, qz1 = std::min(s + L - 1 + qoff, a.N[2] - 1);
         if (qz1 >= qz0) {
             const int64_t cnt = plane * (qz1 - qz0 + 1);
-            hipLaunchKernelGGL(cells_to_coeffs_kernel<n>, dim3((unsigned)((cnt + 255) / 256)), dim3(256), 0, st,
-                               a.scratch, a.N[0], a.N[1], s, L, qz0, qz1, a.coeffs_out);
+            hipLaunchKernelGGL((cells_to_coeffs_kernel<n, SHARED>), dim3((unsigned)((cnt + 255) / 256)), dim3(256), 0,
+                               st, T, a.N[0], a.N[1], s, qz0, qz1, a.coeffs_out);
         }
         if (s + L >= mlo + M2) break;
         s += L - n;
     }
     return hipGetLastError();
+}
+
+template <int n>
+static hipError_t launch_backproject_n(const LaunchArgs &a, hipStream_t st) {
+    if constexpr (n >= 2)
+        if (cells_shared<n>(a.N)) return launch_backproject_cells<n, true>(a, st);
+    return launch_backproject_cells<n, false>(a, st);
 }
 
 hipError_t launch_project_quad(int degree, const LaunchArgs &a, hipStream_t st) {

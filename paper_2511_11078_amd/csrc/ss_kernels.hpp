@@ -39,8 +39,8 @@ struct LaunchArgs {
 };
 
 // Default largest knot-cell table of the quadrature adjoint: 2^34 floats
-// (64 GiB; 256^3 needs 4.45 GB, 512^3 35.6 GB); larger tables are processed
-// in z-chunks of cell layers.  A context may set another limit.
+// (64 GiB; 256^3 needs 0.48 GB, 512^3 3.7 GB at degree 3); larger tables are
+// processed in z-chunks of cell layers.  A context may set another limit.
 constexpr int64_t CELL_SCRATCH_DEFAULT_FLOATS = (int64_t)1 << 34;
 // Table size the quadrature adjoint uses for a volume of N[0] x N[1] x N[2]
 // under a limit of `limit` floats (never below 4 (n+1) cell layers).

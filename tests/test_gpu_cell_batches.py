@@ -86,3 +86,26 @@ def test_axis_parallel_lines_in_some_batches(n, volume):
     e = _adjoint_error(n, geom, VOLUMES[volume], 330 + n)
     say(f"  rel-L2 {e:.3e}")
     assert e <= (1e-5 if n > 0 else 1e-4)
+
+
+@pytest.mark.parametrize("n", [0, 1, 2, 3])
+@pytest.mark.parametrize("dims", [(1, 1, 1), (5, 5, 1), (6, 6, 2), (13, 5, 9), (64, 58, 37)])
+@pytest.mark.parametrize("limit", [0, 1])
+def test_parts_of_blocks(n, dims, limit):
+    """A coefficient's sum over the blocks of cells its support meets: one
+    block, exactly one at degree 3, one cell more, odd counts, and many, in
+    one pass and in z-chunks (the smallest scratch), on every coefficient."""
+    say(f"parts of blocks n={n} {dims} limit {limit}")
+    if n == 1 and dims == (1, 1, 1):
+        pytest.skip("all ten lines that meet it graze its support (footprints below 4.3e-5 of a unit): "
+                    "the one value there is, 1e-5, is below what a bar relative to it can hold in FP32")
+    geom = synth.parallel_geometry(synth.uniform_directions(3, seed=340), 40, 44, pitch=2.1)
+    y = np.random.default_rng(341 + n).standard_normal((3, 40, 44)).astype(np.float32)
+    ctx = Context(n, "quad", 0)
+    ctx.set_scratch_limit(limit)
+    got = to_np(ctx.backproject(to_gpu(y), geom, dims))
+    ctx.close()
+    want = oracle.backproject_subset(y, geom, dims, n)
+    e = rel_l2(got.ravel(), np.asarray(want).ravel())
+    say(f"  rel-L2 {e:.3e}")
+    assert e <= (1e-5 if n > 0 else 1e-4)
