@@ -106,3 +106,22 @@ def test_lane_tiles(n, dims):
     parts = [ctx.project(c, geom.subset_views(v, v + 1)) for v in range(5)]
     assert torch.equal(whole, torch.cat(parts))
     ctx.close()
+
+
+@pytest.mark.parametrize("views,R,C", [(2105, 9, 13), (1, 740, 725), (9, 260, 270), (23, 33, 500)])
+def test_every_tile_of_every_view(views, R, C):
+    """More than 2048 tiles, dealt to the XCDs in items of 2 x 2 tiles of up
+    to eight views: fewer tiles than an item, one view, a last item of one
+    view, odd tile counts.  Every pixel is written, by its own line."""
+    say(f"tiles of {views} views {R}x{C}")
+    dims = (12, 10, 9)
+    geom = synth.parallel_geometry(synth.uniform_directions(views, seed=440), R, C, pitch=14.0 / max(R, C))
+    c = np.random.default_rng(441).uniform(0.5, 1.0, dims[::-1]).astype(np.float32)
+    ctx = Context(1, "quad", 0)
+    out = torch.full((views, R, C), float("nan"), device="cuda")
+    got = to_np(ctx.project(to_gpu(c), geom, out=out))
+    ctx.close()
+    want = oracle.project(c, geom, 1)
+    e = rel_l2(got, want)
+    say(f"  rel-L2 {e:.3e}")
+    assert np.isfinite(got).all() and e <= 1e-5
