@@ -379,6 +379,13 @@ __device__ __forceinline__ void walk_init(Walk<n, STEP> &W, const LineD &L, cons
     if (W.j <= W.j1) W.window();
 }
 
+// Network forwards of up to this many 16 x 16-pixel tiles give a block 16
+// lines instead of 32, so that few lines still make many blocks, and short
+// ones (32 and 16 lines: 36 tiles 0.87 and 0.66 ms, 288 tiles 2.94 and 2.48,
+// 576 tiles at 128^3 11.4 and 9.4, 1152 tiles 8.95 and 8.7, 1728 tiles at
+// 128^3 27.8 and 29.1, 4608 tiles 72.4 and 77.7).
+constexpr int64_t SMALL_TILES = 1024;
+
 // The network forward's pairs waiting to be evaluated, a ring of 128 per
 // wave: the five features, the coefficient's index and the owning lane.
 constexpr int FBUF = 128;
@@ -399,33 +406,36 @@ struct FwdPairBuf {
 // footprint to the owning lane's sum in LDS (atomic adds within the wave),
 // so rounds stay full while some lines of the wave are done and others are
 // not (about 6 % empty slots at cone_256 when each lane evaluated its own
-// pairs).  The four waves of a network block take the same 8 x 8 lines, each
-// every fourth slab of them, and their sums are added in the waves' order:
-// four times as many, shorter blocks, tiles innermost (32^3, 32 views of
-// 48 x 48: 15.5 -> 3.7 ms; 32 views at 128^3: 84 -> 73 ms).
-template <int n, bool EXACT>
+// pairs).  The lanes of a network block's four waves share LINES lines, each
+// group of LINES lanes every (256 / LINES)-th slab of them, and the groups'
+// sums are added in order: many short blocks, tiles innermost (32^3, 32 views
+// of 48 x 48: 15.5 ms with 256 lines a block, 3.75 with 64, 2.48 with 16; 32
+// views at 128^3 84, 73.9 and, with 32, 72.4 ms).
+template <int n, bool EXACT, int LINES = 64>
 __device__ __forceinline__ void project_walk(const float *__restrict__ c, int N0, int N1, int N2,
                                              const float *__restrict__ geom, int kind, int V, int R, int C,
                                              const MlpImage *Wt, float *__restrict__ y, int v, int tr, int tc,
                                              int part = 0, FwdPairBuf *fbuf = nullptr, float *accw = nullptr) {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int quarter = EXACT ? wave : part;  // 8 x 8 pixels of the 16 x 16 tile
-    const int j = tr * 16 + (quarter >> 1) * 8 + (lane >> 3);
-    const int i = tc * 16 + (quarter & 1) * 8 + (lane & 7);
+    // LINES pixels of the 16 x 16 tile, PW in a row
+    constexpr int PW = LINES >= 32 ? 8 : 4, PER_ROW = 16 / PW, GROUPS = 64 / LINES;
+    const int patch = EXACT ? wave : part, line = lane % LINES;
+    const int j = tr * 16 + patch / PER_ROW * (LINES / PW) + line / PW;
+    const int i = tc * 16 + patch % PER_ROW * PW + line % PW;
     const bool pix = v < V && j < R && i < C;
     const int N[3] = {N0, N1, N2};
     const double centre[3] = {0.0, 0.0, 0.0};
     LineD L;
     L.ok = false;
     if (pix) L = make_line(geom + 12 * v, kind, R, C, j, i, centre);
-    Walk<n, EXACT ? 1 : 4> Wk;
+    Walk<n, EXACT ? 1 : 4 * GROUPS> Wk;
     int d = 0, i1 = 1, i2 = 2;
     Fold F;
     Slopes S;
     float inv_wd = 0.0f;
     bool live = false;
     if (L.ok) {
-        walk_init(Wk, L, N, EXACT ? 0 : wave, d, i1, i2);
+        walk_init(Wk, L, N, EXACT ? 0 : wave * GROUPS + lane / LINES, d, i1, i2);
         F = make_fold(L.w);
         S = make_slopes((float)Wk.r1, (float)Wk.r2);
         inv_wd = (float)(1.0 / fabs(pick3(L.w, d)));
@@ -520,15 +530,17 @@ __device__ __forceinline__ void project_walk(const float *__restrict__ c, int N0
     }
     if constexpr (!EXACT) {
         __syncthreads();
-        acc = ((accw[lane] + accw[lane + 64]) + accw[lane + 128]) + accw[lane + 192];
-        if (wave != 0) return;
+        if (threadIdx.x >= LINES) return;
+        acc = accw[line];
+#pragma unroll
+        for (int k = 1; k < 256 / LINES; ++k) acc += accw[k * LINES + line];
     }
     if (pix) y[((int64_t)v * R + j) * C + i] = acc;
 }
 
 // three workgroups (twelve waves) per CU: one wave's matrix-core layers
 // overlap another's SiLU
-template <int n>
+template <int n, int LINES>
 __global__ void __launch_bounds__(256, 3) project_mlp_kernel(const float *__restrict__ c, int N0, int N1, int N2,
                                                           const float *__restrict__ geom, int kind, int V, int R,
                                                           int C, const MlpImage *__restrict__ img,
@@ -536,12 +548,13 @@ __global__ void __launch_bounds__(256, 3) project_mlp_kernel(const float *__rest
     __shared__ MlpImage Wt;
     __shared__ FwdPairBuf fbuf[4];  // one ring per wave of the 256-thread block
     __shared__ float accw[256];
-    // four blocks per 16 x 16-pixel tile, views outermost
+    // 256 / LINES blocks per 16 x 16-pixel tile, views outermost
     const int tR = (R + 15) / 16, tC = (C + 15) / 16;
-    const int part = blockIdx.x & 3, t = blockIdx.x >> 2, tc = t % tC, tr = (t / tC) % tR, v = t / (tC * tR);
+    constexpr int PARTS = 256 / LINES;
+    const int part = blockIdx.x % PARTS, t = blockIdx.x / PARTS, tc = t % tC, tr = (t / tC) % tR, v = t / (tC * tR);
     load_image(Wt, img);
     __syncthreads();
-    project_walk<n, false>(c, N0, N1, N2, geom, kind, V, R, C, &Wt, y, v, tr, tc, part, fbuf, accw);
+    project_walk<n, false, LINES>(c, N0, N1, N2, geom, kind, V, R, C, &Wt, y, v, tr, tc, part, fbuf, accw);
 }
 
 template <int n>
@@ -917,11 +930,19 @@ __global__ void __launch_bounds__(64) footprint_mlp_kernel(const float *__restri
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
+template <int n, int LINES>
+static void launch_project_mlp_lines(const LaunchArgs &a, hipStream_t st) {
+    const int64_t tiles = (int64_t)((a.R + 15) / 16) * ((a.C + 15) / 16) * a.V;
+    hipLaunchKernelGGL((project_mlp_kernel<n, LINES>), dim3((unsigned)(tiles * (256 / LINES))), dim3(256), 0, st,
+                       a.coeffs, a.N[0], a.N[1], a.N[2], a.geom, a.kind, a.V, a.R, a.C, (const MlpImage *)a.mlp,
+                       a.sino);
+}
+
 template <int n>
 static hipError_t launch_project_mlp_n(const LaunchArgs &a, hipStream_t st) {
-    const int tR = (a.R + 15) / 16, tC = (a.C + 15) / 16;
-    hipLaunchKernelGGL(project_mlp_kernel<n>, dim3((unsigned)((int64_t)tR * tC * a.V * 4)), dim3(256), 0, st, a.coeffs, a.N[0], a.N[1],
-                       a.N[2], a.geom, a.kind, a.V, a.R, a.C, (const MlpImage *)a.mlp, a.sino);
+    const int64_t tiles = (int64_t)((a.R + 15) / 16) * ((a.C + 15) / 16) * a.V;
+    if (tiles <= SMALL_TILES) launch_project_mlp_lines<n, 16>(a, st);
+    else launch_project_mlp_lines<n, 32>(a, st);
     return hipGetLastError();
 }
 

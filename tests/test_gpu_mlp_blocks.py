@@ -1,7 +1,7 @@
 """Block shapes of the network form against brute-force pair sums.
 
-Forward blocks take 8 x 8 lines, each of their four waves every fourth slab
-of them; adjoint blocks a brick of 4 x 4 x 4 coefficients, each wave every
+Forward blocks share 8 x 4 lines, or 4 x 4 for up to 1024 tiles of 16 x 16
+pixels, each group of so many lanes some of their slabs; adjoint blocks a brick of 4 x 4 x 4 coefficients, each wave every
 fourth candidate pixel of them, or, for more than 768 bricks of
 8 x 8 x 4, one such brick with a coefficient per thread.  Volumes and
 detectors at the edges of those shapes; the bars are those of the pair
@@ -22,6 +22,8 @@ CASES = {
     # name: (dims, views, rows, cols, pitch)
     "one_coefficient_one_line": ((1, 1, 1), 2, 1, 1, 1.0),
     "one_slab": ((9, 7, 1), 2, 9, 3, 0.9),
+    "last_launch_of_16_lines": ((4, 3, 5), 1024, 1, 2, 1.0),   # 1024 tiles
+    "first_launch_of_32_lines": ((4, 3, 5), 1025, 2, 1, 1.0),
     "one_candidate_column": ((5, 4, 13), 3, 17, 1, 0.3),
     "brick_edges": ((4, 8, 5), 3, 8, 9, 0.8),
     "segments_of_the_line_table": ((5, 3, 4), 2, 40, 21, 0.25),
@@ -48,3 +50,19 @@ def test_blocks_match_pair_enumeration(case):
     say(f"  forward rel-L2 {ef:.3e}, adjoint rel-L2 {eb:.3e}")
     assert np.abs(want_f).max() > 0 and np.abs(want_b).max() > 0
     assert ef <= 2e-5 and eb <= 3e-5
+
+
+def test_line_sharing_rules_agree():
+    """1800 tiles in one launch (32 lines a block) and 900 (16 lines): every
+    line of ragged tiles gets its own sum, to the form's bar."""
+    say("network forward: 32 and 16 lines a block")
+    dims, views = (9, 8, 21), 300
+    geom = tilted_parallel(views, 17, 40, seed=510, pitch=0.6)
+    c = to_gpu(np.random.default_rng(511).uniform(0.2, 1.0, dims[::-1]).astype(np.float32))
+    ctx = Context(3, "mlp", 0)
+    whole = to_np(ctx.project(c, geom))
+    parts = [to_np(ctx.project(c, geom.subset_views(v, v + 150))) for v in (0, 150)]
+    ctx.close()
+    e = rel_l2(whole, np.concatenate(parts))
+    say(f"  rel-L2 {e:.3e}")
+    assert np.abs(whole).max() > 0 and e <= 2e-5
