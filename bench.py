@@ -67,7 +67,7 @@ MLP_TRANS_PER_PAIR = 2 * 4 * 64   # SiLU of 4 x 64 hidden units: one exp and one
 # profiles/cone256_traffic_counters.md.  Valid only for the kernel sources they
 # were measured on (SHA-256 over QUAD_SOURCES); otherwise reported as null.
 QUAD_SOURCES = ["csrc/ss_kernels.hip", "csrc/ss_math.hpp", "csrc/ss_traverse.hpp", "csrc/ss_kernels.hpp"]
-TRAFFIC_SHA256 = "901d0eac1d6ae7cef5840b4e7e52fb39f3a2a45b57f4b0062f9707f6168dd1a0"
+TRAFFIC_SHA256 = "5274bc9b8b451364c82b56aa1d70d3708b8400db31e89798abf4f9e6b1e05751"
 TRAFFIC_BYTES = {  # (kernel, degree) -> (read bytes, written bytes) per application, cone_256
     ("pad_volume_kernel", 3): (2.0 * 36889 * 1024, 1.0 * 71874 * 1024),
     ("pad_volume_zfast_kernel", 3): (2.0 * 65552 * 1024, 1.0 * 72250 * 1024),

@@ -188,7 +188,7 @@ __device__ __forceinline__ float quad_lane(float v) {
 // offset the cell needs, an axis that reaches its plane advances under its
 // own mask (ties advance together instead of by cells of no length), and a
 // row's address is a scalar base plus that one 32-bit offset (WIDE: copies
-// above 4 GiB, 64-bit).  727 -> 640 VALU instructions per (line, cell).
+// above 4 GiB, 64-bit).  727 -> 675 VALU instructions per (line, cell).
 //
 // LPL lanes share a line: LPL = 4 lets a launch of few lines fill the chip
 // (small_parallel_32: 450 -> 115 us for 288 tiles).  Each of the four walks
