@@ -67,18 +67,18 @@ MLP_TRANS_PER_PAIR = 2 * 4 * 64   # SiLU of 4 x 64 hidden units: one exp and one
 # profiles/cone256_traffic_counters.md.  Valid only for the kernel sources they
 # were measured on (SHA-256 over QUAD_SOURCES); otherwise reported as null.
 QUAD_SOURCES = ["csrc/ss_kernels.hip", "csrc/ss_math.hpp", "csrc/ss_traverse.hpp", "csrc/ss_kernels.hpp"]
-TRAFFIC_SHA256 = "5274bc9b8b451364c82b56aa1d70d3708b8400db31e89798abf4f9e6b1e05751"
+TRAFFIC_SHA256 = "38e915dd4a3d90bb462517f68b433044fd2f6ed7a416f29d172103c91ade977f"
 TRAFFIC_BYTES = {  # (kernel, degree) -> (read bytes, written bytes) per application, cone_256
-    ("pad_volume_kernel", 3): (2.0 * 36889 * 1024, 1.0 * 71874 * 1024),
-    ("pad_volume_zfast_kernel", 3): (2.0 * 65552 * 1024, 1.0 * 72250 * 1024),
+    ("pad_volume_kernel", 3): (2.0 * 36890 * 1024, 1.0 * 71874 * 1024),
+    ("pad_volume_zfast_kernel", 3): (2.0 * 65552 * 1024, 1.0 * 72251 * 1024),
     ("pad_volume_yfast_kernel", 3): (0.0, 0.0),  # a y-fastest copy is no longer made
-    ("project_kernel", 3): (2.0 * 4313704 * 1024, 1.0 * 278744 * 1024),
-    ("backproject_cells_kernel", 3): (2.0 * 3169712 * 1024, 1.0 * 468950 * 1024),
-    ("cells_to_coeffs_kernel", 3): (2.0 * 521236 * 1024, 1.0 * 65536 * 1024),
-    ("pad_volume_zfast_kernel", 0): (2.0 * 65555 * 1024, 1.0 * 80262 * 1024),
+    ("project_kernel", 3): (2.0 * 4311136 * 1024, 1.0 * 278135 * 1024),
+    ("backproject_cells_kernel", 3): (2.0 * 3169191 * 1024, 1.0 * 468950 * 1024),
+    ("cells_to_coeffs_kernel", 3): (2.0 * 521237 * 1024, 1.0 * 65536 * 1024),
+    ("pad_volume_zfast_kernel", 0): (2.0 * 65555 * 1024, 1.0 * 80263 * 1024),
     ("pad_volume_kernel", 0): (2.0 * 36888 * 1024, 1.0 * 67084 * 1024),
-    ("project_kernel", 0): (2.0 * 3471111 * 1024, 1.0 * 289895 * 1024),
-    ("backproject_cells_kernel", 0): (2.0 * 3136231 * 1024, 1.0 * 65536 * 1024),
+    ("project_kernel", 0): (2.0 * 3471147 * 1024, 1.0 * 290100 * 1024),
+    ("backproject_cells_kernel", 0): (2.0 * 3136771 * 1024, 1.0 * 65536 * 1024),
     ("cells_to_coeffs_kernel", 0): (2.0 * 131094 * 1024, 1.0 * 65536 * 1024),
 }
 
@@ -92,13 +92,13 @@ L2_FILL_BYTES = {  # (kernel, degree) -> bytes per application, cone_256
     ("pad_volume_kernel", 3): 128.0 * 589824,
     ("pad_volume_zfast_kernel", 3): 128.0 * 1048576,
     ("pad_volume_yfast_kernel", 3): 0.0,
-    ("project_kernel", 3): 128.0 * 11563939089,
-    ("backproject_cells_kernel", 3): 128.0 * 270088405,
-    ("cells_to_coeffs_kernel", 3): 128.0 * 10353583,
+    ("project_kernel", 3): 128.0 * 11564400167,
+    ("backproject_cells_kernel", 3): 128.0 * 270085298,
+    ("cells_to_coeffs_kernel", 3): 128.0 * 10364300,
     ("pad_volume_zfast_kernel", 0): 128.0 * 1048576,
     ("pad_volume_kernel", 0): 128.0 * 589824,
-    ("project_kernel", 0): 128.0 * 2101073338,
-    ("backproject_cells_kernel", 0): 128.0 * 250958282,
+    ("project_kernel", 0): 128.0 * 2101719036,
+    ("backproject_cells_kernel", 0): 128.0 * 250965735,
     ("cells_to_coeffs_kernel", 0): 128.0 * 2097152,
 }
 PEAK_L2_TBS = 8 * 16 * 128 * 2.4e9 / 1e12

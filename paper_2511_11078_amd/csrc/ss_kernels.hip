@@ -109,8 +109,13 @@ __device__ __forceinline__ ViewWalk view_walk(const float *__restrict__ e, int k
 // ---------------------------------------------------------------------------
 
 // Launches of up to this many 16 x 16-pixel tiles share each line among four
-// lanes (project_kernel).
-constexpr int64_t FWD_SHARED_TILES = 2048;
+// lanes (project_kernel), by degree: all four walk the whole line, so the
+// shorter the integral the sooner that costs more than it gives.  Shared and
+// not, us: degree 0 490 tiles 60 and 62, 540 tiles 37 and 28, 960 tiles 207
+// and 148; degree 1 280 tiles 55 and 69, 384 tiles 202 and 192, 980 tiles 127
+// and 109; degree 2 700 tiles 167 and 249, 960 tiles 527 and 442; degree 3
+// 980 tiles 360 and 497, 1440 tiles 284 and 297, 1920 tiles 1780 and 1364.
+constexpr int64_t FWD_SHARED_TILES[4] = {512, 320, 768, 1536};
 // Copies of up to this many floats (128 MiB) are walked in waves of 8 x 8
 // pixels instead of 16 x 4 at degrees 2 and 3.  Square waves idle less where
 // lines leave the volume (16 x 4 against 8 x 8: 128^3 with 192^2 pixels
@@ -1165,7 +1170,7 @@ static hipError_t launch_project_n(const LaunchArgs &a, hipStream_t st) {
     if (zb > INT32_MAX) return hipErrorInvalidValue;
     const auto walk = [&](const float *cz, const float *cx, int which) {
         if (padded > (int64_t)1 << 30) launch_walk<n, 1, true>(a, cz, cx, which, st);
-        else if ((int64_t)((a.R + 15) / 16) * ((a.C + 15) / 16) * a.V <= FWD_SHARED_TILES)
+        else if ((int64_t)((a.R + 15) / 16) * ((a.C + 15) / 16) * a.V <= FWD_SHARED_TILES[n])
             launch_walk<n, 4, false>(a, cz, cx, which, st);
         else launch_walk<n, 1, false>(a, cz, cx, which, st);
     };
