@@ -758,10 +758,14 @@ __device__ __forceinline__ void backproject_gather(const float *__restrict__ y, 
                 const int i0 = max(mi0, ci0), i1 = min(mi1, ci1);
                 int jj = j0, ii = i0 + first;
                 bool live = j0 <= j1 && i0 <= i1 && !rest;
-                const int ni = i1 - i0 + 1;
+                [[maybe_unused]] const int ni = i1 - i0 + 1;
                 // to the pixel WAVES further on
                 const auto wrap = [&] {
-                    while (ii > i1 && jj <= j1) { ii -= ni; ++jj; }
+                    if constexpr (WAVES == 1) {  // at most one row on
+                        if (ii > i1) { ii = i0; ++jj; }
+                    } else {
+                        while (ii > i1 && jj <= j1) { ii -= ni; ++jj; }
+                    }
                     live = live && jj <= j1;
                 };
                 if (live) wrap();
