@@ -22,6 +22,7 @@
 // weight image (built on the host from the blob) bakes this permutation
 // into the A operands, so activations never leave their lane.
 #include "ss_kernels.hpp"
+#include "ss_launch.hpp"
 
 #include <cstring>
 
@@ -544,14 +545,16 @@ template <int n, int LINES>
 __global__ void __launch_bounds__(256, 3) project_mlp_kernel(const float *__restrict__ c, int N0, int N1, int N2,
                                                           const float *__restrict__ geom, int kind, int V, int R,
                                                           int C, const MlpImage *__restrict__ img,
-                                                          float *__restrict__ y) {
+                                                          float *__restrict__ y, int t0) {
     __shared__ MlpImage Wt;
     __shared__ FwdPairBuf fbuf[4];  // one ring per wave of the 256-thread block
     __shared__ float accw[256];
-    // 256 / LINES blocks per 16 x 16-pixel tile, views outermost
+    // 256 / LINES blocks per 16 x 16-pixel tile, views outermost; the
+    // launch's first tile is t0
     const int tR = (R + 15) / 16, tC = (C + 15) / 16;
     constexpr int PARTS = 256 / LINES;
-    const int part = blockIdx.x % PARTS, t = blockIdx.x / PARTS, tc = t % tC, tr = (t / tC) % tR, v = t / (tC * tR);
+    const int part = blockIdx.x % PARTS, t = t0 + (int)(blockIdx.x / PARTS), tc = t % tC, tr = (t / tC) % tR;
+    const int v = t / (tC * tR);
     load_image(Wt, img);
     __syncthreads();
     project_walk<n, false, LINES>(c, N0, N1, N2, geom, kind, V, R, C, &Wt, y, v, tr, tc, part, fbuf, accw);
@@ -937,9 +940,12 @@ __global__ void __launch_bounds__(64) footprint_mlp_kernel(const float *__restri
 template <int n, int LINES>
 static void launch_project_mlp_lines(const LaunchArgs &a, hipStream_t st) {
     const int64_t tiles = (int64_t)((a.R + 15) / 16) * ((a.C + 15) / 16) * a.V;
-    hipLaunchKernelGGL((project_mlp_kernel<n, LINES>), dim3((unsigned)(tiles * (256 / LINES))), dim3(256), 0, st,
-                       a.coeffs, a.N[0], a.N[1], a.N[2], a.geom, a.kind, a.V, a.R, a.C, (const MlpImage *)a.mlp,
-                       a.sino);
+    constexpr int PARTS = 256 / LINES;
+    in_pieces(tiles, 256 * PARTS, [&](int64_t t0, int64_t count) {
+        hipLaunchKernelGGL((project_mlp_kernel<n, LINES>), dim3((unsigned)(count * PARTS)), dim3(256), 0, st, a.coeffs,
+                           a.N[0], a.N[1], a.N[2], a.geom, a.kind, a.V, a.R, a.C, (const MlpImage *)a.mlp, a.sino,
+                           (int)t0);
+    });
 }
 
 template <int n>

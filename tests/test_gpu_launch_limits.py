@@ -1,0 +1,40 @@
+"""Calls whose blocks do not fit one launch (HIP: fewer than 2^32 threads)."""
+import numpy as np
+import pytest
+
+from paper_2511_11078_amd import synth
+from paper_2511_11078_amd.ops import Context
+
+from gpu_helpers import rel_l2, say, to_gpu, to_np
+
+pytestmark = pytest.mark.gpu
+
+
+def _row(w, u, v, pitch, C, centre):
+    """One view of one row of C columns, `centre` along u from the origin."""
+    return synth.Geometry("parallel", 1, 1, C, np.concatenate([w, centre * u, pitch * u, v])[None].astype(np.float32))
+
+
+def test_network_forward_of_more_than_2_21_tiles():
+    """One row of 16 x 2^21 + 40 columns is three tiles more than one launch of
+    eight blocks a tile takes.  The volume lies before its last 400,000
+    columns: those are compared with a row of every 64th of them, the others
+    see nothing.  The rows' FP32 centres and pitches put a line up to 6e-5 of
+    a coefficient's width apart (335 of them times 2^-24, twice, and the
+    centre's own rounding); sums change by no more than their own size per
+    such width, and 5e-4 leaves eight times that."""
+    C, Cs, step, pitch = 16 * 2**21 + 40, 8192, 64, 2.0e-5
+    say(f"network forward, one row of {C} columns")
+    w = np.array([1.0, 0.3, 0.2]) / np.linalg.norm([1.0, 0.3, 0.2])
+    u, v = synth.detector_frame(w)
+    centre = -pitch * (C - 1) / 2 + 4.0  # the last column is 4 beyond the volume's centre
+    wide = _row(w, u, v, pitch, C, centre)
+    few = _row(w, u, v, pitch * step, Cs, centre + pitch * ((C - 1) / 2 - step * (Cs - 1) / 2))
+    c = to_gpu(np.random.default_rng(530).uniform(0.2, 1.0, (4, 5, 6)).astype(np.float32))
+    ctx = Context(1, "mlp", 0)
+    got, want = to_np(ctx.project(c, wide)).ravel(), to_np(ctx.project(c, few)).ravel()
+    ctx.close()
+    e = rel_l2(got[C - 1 - step * (Cs - 1)::step], want)
+    say(f"  rel-L2 {e:.3e}, non-zero {np.count_nonzero(want)} of {Cs}")
+    assert np.count_nonzero(want) > 1000 and e <= 5e-4
+    assert np.count_nonzero(got[:C - step * Cs]) == 0
