@@ -18,6 +18,7 @@
 #include "splinesplat.h"
 #include "ss_geom_upload.hpp"
 #include "ss_kernels.hpp"
+#include "ss_scratch.hpp"
 
 struct ss_ctx {
     int device = 0;
@@ -27,8 +28,7 @@ struct ss_ctx {
     hipEvent_t staged = nullptr;    // marks the end of the last upload's read of the staging buffer
     double *d_partials = nullptr;   // dot-product partial sums
     void *d_mlp = nullptr;          // network weights in kernel layout
-    float *d_cells = nullptr;       // quadrature scratch: padded coefficients (forward), knot-cell table (adjoint)
-    int64_t cells_cap = 0;          // floats
+    ss::ScratchBuffer cells;        // quadrature scratch: padded coefficients (forward), knot-cell table (adjoint)
     int64_t cell_limit = ss::CELL_SCRATCH_DEFAULT_FLOATS;  // largest knot-cell table (floats)
 };
 
@@ -174,24 +174,35 @@ ss_status upload_geom(ss_ctx *ctx, const ss_geometry *g, hipStream_t st) {
     return fail(SS_EDEVICE, "geometry upload failed");
 }
 
-// Make the quadrature scratch (padded copies of the coefficients for the forward, the
-// knot-cell table for the adjoint) hold at least `need` floats.
-ss_status ensure_cells(ss_ctx *ctx, int64_t need) {
-    if (need <= ctx->cells_cap) return SS_OK;
-    hipError_t e;
-    if (ctx->d_cells) {
-        // the old table may still be in use by enqueued work: wait for it
-        if ((e = hipDeviceSynchronize()) != hipSuccess) return hip_fail(e, "hipDeviceSynchronize");
-        (void)hipFree(ctx->d_cells);
-        ctx->d_cells = nullptr;
-        ctx->cells_cap = 0;
+// HIP device operations of the quadrature scratch (ss_scratch.hpp).
+struct HipScratchOps {
+    hipStream_t st;
+    int dev_alloc(void **p, size_t bytes) {
+        const hipError_t e = hipMalloc(p, bytes);
+        if (e != hipSuccess) (void)hipGetLastError();
+        return (int)e;
     }
-    if ((e = hipMalloc(&ctx->d_cells, (size_t)need * sizeof(float))) != hipSuccess) {
-        ctx->d_cells = nullptr;
-        return fail(SS_ENOMEM, "quadrature scratch (%lld bytes): %s", (long long)need * 4, hipGetErrorString(e));
+    void dev_free(void *p) { (void)hipFree(p); }
+    int device_sync() { return (int)hipDeviceSynchronize(); }
+    bool capturing() {
+        hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+        return hipStreamIsCapturing(st, &s) != hipSuccess || s != hipStreamCaptureStatusNone;
     }
-    ctx->cells_cap = need;
-    return SS_OK;
+};
+
+// Make the quadrature scratch (padded copies of the coefficients for the
+// forward, the knot-cell table for the adjoint) hold at least `need` floats,
+// and `want` where they can be had.
+ss_status ensure_cells(ss_ctx *ctx, int64_t need, int64_t want, hipStream_t st) {
+    HipScratchOps ops{st};
+    int code = 0;
+    switch (ctx->cells.hold(ops, need, want, &code)) {
+    case ss::SCRATCH_OK: return SS_OK;
+    case ss::SCRATCH_SYNC: return hip_fail((hipError_t)code, "hipDeviceSynchronize");
+    case ss::SCRATCH_ALLOC: break;
+    }
+    return fail(SS_ENOMEM, "quadrature scratch (%lld bytes): %s", (long long)need * 4,
+                hipGetErrorString((hipError_t)code));
 }
 
 ss_status check_ctx(const ss_ctx *ctx) {
@@ -279,7 +290,7 @@ ss_status ss_destroy(ss_ctx *ctx) {
     if (ctx->staged) (void)hipEventDestroy(ctx->staged);
     if (ctx->d_partials) (void)hipFree(ctx->d_partials);
     if (ctx->d_mlp) (void)hipFree(ctx->d_mlp);
-    if (ctx->d_cells) (void)hipFree(ctx->d_cells);
+    if (ctx->cells.p) (void)hipFree(ctx->cells.p);
     delete ctx;
     return SS_OK;
 }
@@ -313,12 +324,9 @@ static ss_status run_transform(ss_ctx *ctx, bool forward, const float *in, const
         if (ctx->form == SS_FORM_QUAD_FP32) {
             const int64_t one = ss::project_quad_scratch_floats(ctx->degree, a.N);
             const int64_t all = one * ss::project_quad_copies(ctx->degree, a.N);
-            if (all > ctx->cell_limit || ensure_cells(ctx, all) != SS_OK) {
-                (void)hipGetLastError();  // of a second copy that does not fit
-                if (ss_status s = ensure_cells(ctx, one)) return s;
-            }
-            a.scratch = ctx->d_cells;
-            a.scratch_floats = ctx->cells_cap;
+            if (ss_status s = ensure_cells(ctx, one, all <= ctx->cell_limit ? all : one, st)) return s;
+            a.scratch = ctx->cells.p;
+            a.scratch_floats = ctx->cells.cap;
         }
         e = ctx->form == SS_FORM_QUAD_FP32   ? ss::launch_project_quad(ctx->degree, a, st)
             : ctx->form == SS_FORM_MLP_BF16  ? ss::launch_project_mlp(ctx->degree, a, st)
@@ -328,8 +336,8 @@ static ss_status run_transform(ss_ctx *ctx, bool forward, const float *in, const
         a.coeffs_out = out;
         if (ctx->form == SS_FORM_QUAD_FP32) {
             const int64_t need = ss::backproject_quad_scratch_floats(ctx->degree, a.N, ctx->cell_limit);
-            if (ss_status s = ensure_cells(ctx, need)) return s;
-            a.scratch = ctx->d_cells;
+            if (ss_status s = ensure_cells(ctx, need, need, st)) return s;
+            a.scratch = ctx->cells.p;
             a.scratch_floats = need;  // the chunking follows the limit, not the buffer's size
         }
         e = ctx->form == SS_FORM_QUAD_FP32   ? ss::launch_backproject_quad(ctx->degree, a, st)
@@ -398,15 +406,14 @@ ss_status ss_set_scratch_limit(ss_ctx *ctx, size_t bytes) {
     const int64_t floats = bytes == 0 ? ss::CELL_SCRATCH_DEFAULT_FLOATS
                                       : (int64_t)std::min<size_t>(bytes / sizeof(float), (size_t)1 << 40);
     ctx->cell_limit = floats;
-    if (ctx->d_cells && ctx->cells_cap > floats) {
+    ctx->cells.refused = INT64_MAX;
+    if (ctx->cells.cap > floats) {
         // release a buffer above the new limit (enqueued work may still use it)
         DeviceGuard guard(ctx->device);
         if (guard.err != hipSuccess) return hip_fail(guard.err, "hipSetDevice");
-        hipError_t e;
-        if ((e = hipDeviceSynchronize()) != hipSuccess) return hip_fail(e, "hipDeviceSynchronize");
-        (void)hipFree(ctx->d_cells);
-        ctx->d_cells = nullptr;
-        ctx->cells_cap = 0;
+        HipScratchOps ops{nullptr};
+        if (const int e = ops.device_sync()) return hip_fail((hipError_t)e, "hipDeviceSynchronize");
+        ctx->cells.drop(ops);
     }
     return SS_OK;
 }
