@@ -67,19 +67,19 @@ MLP_TRANS_PER_PAIR = 2 * 4 * 64   # SiLU of 4 x 64 hidden units: one exp and one
 # profiles/cone256_traffic_counters.md.  Valid only for the kernel sources they
 # were measured on (SHA-256 over QUAD_SOURCES); otherwise reported as null.
 QUAD_SOURCES = ["csrc/ss_kernels.hip", "csrc/ss_math.hpp", "csrc/ss_traverse.hpp", "csrc/ss_kernels.hpp"]
-TRAFFIC_SHA256 = "38e915dd4a3d90bb462517f68b433044fd2f6ed7a416f29d172103c91ade977f"
+TRAFFIC_SHA256 = "9c06fea0d9413ea622ae0813c177fa585e596ae3c85137d9ea5fd560ff10fa79"
 TRAFFIC_BYTES = {  # (kernel, degree) -> (read bytes, written bytes) per application, cone_256
-    ("pad_volume_kernel", 3): (2.0 * 36890 * 1024, 1.0 * 71874 * 1024),
-    ("pad_volume_zfast_kernel", 3): (2.0 * 65552 * 1024, 1.0 * 72251 * 1024),
+    ("pad_volume_kernel", 3): (2.0 * 36888 * 1024, 1.0 * 71874 * 1024),
+    ("pad_volume_zfast_kernel", 3): (2.0 * 65556 * 1024, 1.0 * 72252 * 1024),
     ("pad_volume_yfast_kernel", 3): (0.0, 0.0),  # a y-fastest copy is no longer made
-    ("project_kernel", 3): (2.0 * 4311136 * 1024, 1.0 * 278135 * 1024),
-    ("backproject_cells_kernel", 3): (2.0 * 3169191 * 1024, 1.0 * 468950 * 1024),
-    ("cells_to_coeffs_kernel", 3): (2.0 * 521237 * 1024, 1.0 * 65536 * 1024),
-    ("pad_volume_zfast_kernel", 0): (2.0 * 65555 * 1024, 1.0 * 80263 * 1024),
-    ("pad_volume_kernel", 0): (2.0 * 36888 * 1024, 1.0 * 67084 * 1024),
-    ("project_kernel", 0): (2.0 * 3471147 * 1024, 1.0 * 290100 * 1024),
-    ("backproject_cells_kernel", 0): (2.0 * 3136771 * 1024, 1.0 * 65536 * 1024),
-    ("cells_to_coeffs_kernel", 0): (2.0 * 131094 * 1024, 1.0 * 65536 * 1024),
+    ("project_kernel", 3): (2.0 * 4317327 * 1024, 1.0 * 280673 * 1024),
+    ("backproject_cells_kernel", 3): (2.0 * 3169515 * 1024, 1.0 * 468950 * 1024),
+    ("cells_to_coeffs_kernel", 3): (2.0 * 521234 * 1024, 1.0 * 65536 * 1024),
+    ("pad_volume_zfast_kernel", 0): (2.0 * 65555 * 1024, 1.0 * 79973 * 1024),
+    ("pad_volume_kernel", 0): (2.0 * 36889 * 1024, 1.0 * 67084 * 1024),
+    ("project_kernel", 0): (2.0 * 3473588 * 1024, 1.0 * 289848 * 1024),
+    ("backproject_cells_kernel", 0): (2.0 * 3136587 * 1024, 1.0 * 65536 * 1024),
+    ("cells_to_coeffs_kernel", 0): (2.0 * 131092 * 1024, 1.0 * 65536 * 1024),
 }
 
 
@@ -92,13 +92,13 @@ L2_FILL_BYTES = {  # (kernel, degree) -> bytes per application, cone_256
     ("pad_volume_kernel", 3): 128.0 * 589824,
     ("pad_volume_zfast_kernel", 3): 128.0 * 1048576,
     ("pad_volume_yfast_kernel", 3): 0.0,
-    ("project_kernel", 3): 128.0 * 11564400167,
-    ("backproject_cells_kernel", 3): 128.0 * 270085298,
-    ("cells_to_coeffs_kernel", 3): 128.0 * 10364300,
+    ("project_kernel", 3): 128.0 * 11913602196,
+    ("backproject_cells_kernel", 3): 128.0 * 270079963,
+    ("cells_to_coeffs_kernel", 3): 128.0 * 10366518,
     ("pad_volume_zfast_kernel", 0): 128.0 * 1048576,
     ("pad_volume_kernel", 0): 128.0 * 589824,
-    ("project_kernel", 0): 128.0 * 2101719036,
-    ("backproject_cells_kernel", 0): 128.0 * 250965735,
+    ("project_kernel", 0): 128.0 * 2099208305,
+    ("backproject_cells_kernel", 0): 128.0 * 250961585,
     ("cells_to_coeffs_kernel", 0): 128.0 * 2097152,
 }
 PEAK_L2_TBS = 8 * 16 * 128 * 2.4e9 / 1e12
@@ -383,9 +383,10 @@ def main():
                 fl_a = (R * cells_per_ray * adj_unit_flops(n) + ncells * adj_cell_flops(n)
                         + nb3 * float(np.prod(dims)))
                 # each view is walked in one of two copies of the
-                # coefficients (z or x fastest): two pads, one launch
-                fwd_name = (f"pad_volume_zfast_kernel + pad_volume_kernel + project_kernel<{n}> "
-                            f"(knot-cell walk)")
+                # coefficients, z or (some views of the parallel workloads)
+                # x fastest: a pad for each, one launch
+                fwd_name = ("pad_volume_zfast_kernel + " + ("pad_volume_kernel + " if geom.kind == "parallel" else "") +
+                            f"project_kernel<{n}> (knot-cell walk)")
                 for name, ms, fl, unit in (
                         (fwd_name, fwd_ms, fl_f,
                          f"{fwd_unit_flops(n):.0f} flop per (line, cell) x {cells_per_ray:.1f} cells/line"),

@@ -129,9 +129,10 @@ ss_status ss_destroy(ss_ctx *ctx);
  * d_sino: FP32 [n_views][det_rows][det_cols], overwritten.
  * With SS_FORM_QUAD_FP32 the context's device scratch (the one described
  * at ss_backproject) first receives a zero-padded copy of d_coeffs,
- * (dims + 2 degree + 2) floats per axis, and a second one in another order
- * where both take up to 2 GiB, fit the scratch limit and can be allocated
- * (otherwise the two share one place in turn; the result is the same).
+ * (dims + 2 degree + 2) floats per axis, and, for views whose detector runs
+ * better along x than along z, a second one in another order where both take
+ * up to 2 GiB, fit the scratch limit and can be allocated (otherwise the two
+ * share one place in turn; the result is the same).
  * Errors: SS_EINVAL (null pointers, dims < 1 or > 4096, non-finite vecs,
  * zero-length ray direction, more than 2^31 rays per call), SS_ENOMEM. */
 ss_status ss_project(ss_ctx *ctx, const float *d_coeffs, const int64_t dims[3],

@@ -25,6 +25,7 @@ struct ss_ctx {
     int degree = 3;
     int form = SS_FORM_QUAD_FP32;
     ss::GeomBuffer geom;            // device copy of the last geometry, pinned staging, upload cache
+    bool geom_walks_x = false;      // whether the quadrature forward makes the x-fastest copy for `geom`'s views
     hipEvent_t staged = nullptr;    // marks the end of the last upload's read of the staging buffer
     double *d_partials = nullptr;   // dot-product partial sums
     void *d_mlp = nullptr;          // network weights in kernel layout
@@ -159,6 +160,7 @@ ss_status upload_geom(ss_ctx *ctx, const ss_geometry *g, hipStream_t st) {
     auto fill = [&](float *stage) {
         ss::ViewProj *vp = reinterpret_cast<ss::ViewProj *>(stage + vp_off);
         for (size_t v = 0; v < nv; ++v) ss::make_viewproj(g->vecs + 12 * v, (int)g->kind, vp[v]);
+        ctx->geom_walks_x = ss::project_quad_walks_x(ctx->degree, g->vecs, g->n_views, (int)g->kind);
     };
     int code = 0;
     const ss::UploadError r = ctx->geom.upload(ops, g->vecs, nf, (int)g->kind, total, fill, &code);
@@ -323,7 +325,8 @@ static ss_status run_transform(ss_ctx *ctx, bool forward, const float *in, const
         a.sino = out;
         if (ctx->form == SS_FORM_QUAD_FP32) {
             const int64_t one = ss::project_quad_scratch_floats(ctx->degree, a.N);
-            const int64_t all = one * ss::project_quad_copies(ctx->degree, a.N);
+            a.walks_x = ctx->geom_walks_x;
+            const int64_t all = one * ss::project_quad_copies(ctx->degree, a.N, a.walks_x);
             if (ss_status s = ensure_cells(ctx, one, all <= ctx->cell_limit ? all : one, st)) return s;
             a.scratch = ctx->cells.p;
             a.scratch_floats = ctx->cells.cap;
@@ -397,6 +400,7 @@ ss_status ss_project_noalloc(int device, int degree, const float *d_coeffs, cons
     a.C = geom->det_cols;
     a.scratch = base + geom_floats;
     a.scratch_floats = ss::STATIC_SCRATCH_FLOATS - geom_floats;
+    a.walks_x = ss::project_quad_walks_x(degree, geom->vecs, geom->n_views, (int)geom->kind);
     if ((e = ss::launch_project_quad(degree, a, st)) != hipSuccess) return hip_fail(e, "project launch");
     return SS_OK;
 }

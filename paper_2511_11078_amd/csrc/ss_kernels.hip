@@ -73,11 +73,16 @@ __global__ void __launch_bounds__(256) pad_volume_zfast_kernel(const float *__re
 // `yorder`: which of x and y is contracted first (y: central ray within 15
 // degrees of x, or between 15 and 35 degrees of y).  It has no bearing on
 // speed; it fixes the order of the FP32 sums.
+//
+// The host evaluates it too (project_quad_walks_x): a geometry none of whose
+// views fits x better, as every circular trajectory about z, makes and holds
+// the z-fastest copy alone (two: 0.05 + 0.04 ms and 147 MB on cone_256; a
+// degree-0 call of 16^3 15.9 and 12.5 us).
 struct ViewWalk {
     bool yorder, xcopy, rows;  // rows: lanes along the detector's rows
 };
 template <int n>
-__device__ __forceinline__ ViewWalk view_walk(const float *__restrict__ e, int kind) {
+__host__ __device__ __forceinline__ ViewWalk view_walk(const float *__restrict__ e, int kind) {
     ViewWalk vw;
     float d[3];
 #pragma unroll
@@ -182,7 +187,8 @@ __device__ __forceinline__ float quad_lane(float v) {
 }
 
 // `which` = 2: every view, each in the copy it walks (view_walk; both copies
-// are there).  0 and 1: only the views of the z- and of the x-fastest copy
+// are there, or, cx null, the z-fastest one alone, which then serves a view
+// whose two cosines tie but for rounding as well).  0 and 1: only the views of the z- and of the x-fastest copy
 // (blocks of the others return at once), for a scratch that holds one copy
 // at a time.
 //
@@ -224,7 +230,8 @@ __global__ void __launch_bounds__(256, n == 3 ? 3 : 4) project_kernel(const floa
         v = t / (tC * tR);
     }
     if (v >= V) return;
-    const ViewWalk vw = view_walk<n>(geom + 12 * v, kind);
+    ViewWalk vw = view_walk<n>(geom + 12 * v, kind);
+    if (!cx) vw.xcopy = false;
     if (which != 2 && vw.xcopy != (which != 0)) return;  // the other copy's view
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int sub = lane & (LPL - 1);
@@ -1174,13 +1181,17 @@ static hipError_t launch_project_n(const LaunchArgs &a, hipStream_t st) {
             launch_walk<n, 4, false>(a, cz, cx, which, st);
         else launch_walk<n, 1, false>(a, cz, cx, which, st);
     };
-    // the x-fastest copy beside the z-fastest one, or, where the scratch
-    // holds one, in its place after a launch for the views of the other
-    // (stream order)
+    // the x-fastest copy, for the views that walk it, beside the z-fastest
+    // one or, where the scratch holds one, in its place after a launch for
+    // the views of the other (stream order)
     const bool both = a.scratch_floats >= 2 * padded;
-    float *cz = a.scratch, *cx = both ? a.scratch + padded : a.scratch;
+    float *cz = a.scratch, *cx = !a.walks_x ? nullptr : both ? a.scratch + padded : a.scratch;
     hipLaunchKernelGGL(pad_volume_zfast_kernel, dim3((unsigned)zb), dim3(256), 0, st, a.coeffs, a.N[0], a.N[1], a.N[2],
                        P, cz);
+    if (!cx) {
+        walk(cz, cx, 2);
+        return hipGetLastError();
+    }
     if (!both) walk(cz, cx, 0);
     hipLaunchKernelGGL(pad_volume_kernel, dim3((unsigned)std::min<int64_t>((padded + 255) / 256, 65536)), dim3(256), 0,
                        st, a.coeffs, a.N[0], a.N[1], a.N[2], P, cx);
@@ -1193,8 +1204,20 @@ int64_t project_quad_scratch_floats(int degree, const int N[3]) {
     return (N[0] + 2 * P) * (N[1] + 2 * P) * (N[2] + 2 * P);
 }
 
-int project_quad_copies(int degree, const int N[3]) {
-    return project_quad_scratch_floats(degree, N) <= FWD_BOTH_FLOATS ? 2 : 1;
+int project_quad_copies(int degree, const int N[3], bool walks_x) {
+    return walks_x && project_quad_scratch_floats(degree, N) <= FWD_BOTH_FLOATS ? 2 : 1;
+}
+
+template <int n> static bool walks_x_n(const float *vecs, int V, int kind) {
+    for (int v = 0; v < V; ++v)
+        if (view_walk<n>(vecs + 12 * (int64_t)v, kind).xcopy) return true;
+    return false;
+}
+
+bool project_quad_walks_x(int degree, const float *vecs, int V, int kind) {
+    // the contraction order, which keeps a view from the x-fastest copy, is
+    // the same at every degree but 0
+    return degree == 0 ? walks_x_n<0>(vecs, V, kind) : walks_x_n<1>(vecs, V, kind);
 }
 
 // Whether the adjoint of a volume shares each cell's moments, and the floats

@@ -36,6 +36,7 @@ struct LaunchArgs {
     const void *mlp;       // device weights (network form)
     float *scratch;        // quadrature forward: padded coefficients; adjoint: knot-cell table
     int64_t scratch_floats;
+    bool walks_x;          // quadrature forward: some view walks the x-fastest copy
 };
 
 // Default largest knot-cell table of the quadrature adjoint: 2^34 floats
@@ -48,9 +49,12 @@ int64_t backproject_quad_scratch_floats(int degree, const int N[3], int64_t limi
 // Zero-padded copy of the coefficients the quadrature forward walks.
 #define FWD_PAD(n) ((n) + 1)
 int64_t project_quad_scratch_floats(int degree, const int N[3]);
+// Whether the forward walks any of these views (12 host floats each) in the
+// x-fastest copy.
+bool project_quad_walks_x(int degree, const float *vecs, int V, int kind);
 // Copies of that size the forward uses if the scratch holds them (one is
 // enough; with two, one launch walks every view).
-int project_quad_copies(int degree, const int N[3]);
+int project_quad_copies(int degree, const int N[3], bool walks_x);
 
 hipError_t launch_project_quad(int degree, const LaunchArgs &a, hipStream_t st);
 
