@@ -210,7 +210,7 @@ __global__ void __launch_bounds__(256, n == 3 ? 3 : 4) project_kernel(const floa
                                                                      const float *__restrict__ cx, int N0, int N1,
                                                                      int N2, const float *__restrict__ geom, int kind,
                                                                      int V, int R, int C, float *__restrict__ y,
-                                                                     int which) {
+                                                                     int which, int nv) {
     constexpr int NB = n + 1;
     constexpr double h = (double)Degree<n>::h;
     constexpr double kap = (double)Degree<n>::kap;
@@ -219,7 +219,7 @@ __global__ void __launch_bounds__(256, n == 3 ? 3 : 4) project_kernel(const floa
     const int tR = (R + 15) / 16, tC = (C + 15) / 16;
     int v, tr, tc_, part = 0;
     if constexpr (LPL == 1) {
-        if (!fwd_block_tile(V, tR, tC, v, tr, tc_)) return;  // padding slot
+        if (!fwd_block_tile(V, nv, tR, tC, v, tr, tc_)) return;  // padding slot
     } else {
         // four blocks per 16 x 16-pixel tile, tiles innermost: a launch this
         // small spreads evenly, and its volume stays in every L2
@@ -1163,9 +1163,14 @@ __global__ void xpay_kernel(const double *__restrict__ beta, const float *__rest
 template <int n, int LPL, bool WIDE>
 static void launch_walk(const LaunchArgs &a, const float *cz, const float *cx, int which, hipStream_t st) {
     const int tR = (a.R + 15) / 16, tC = (a.C + 15) / 16;
-    const int64_t nb = LPL == 1 ? fwd_blocks(tR, tC, a.V) : (int64_t)tR * tC * a.V * LPL;
-    hipLaunchKernelGGL((project_kernel<n, LPL, WIDE>), dim3((unsigned)nb), dim3(256), 0, st, cz, cx, a.N[0], a.N[1],
-                       a.N[2], a.geom, a.kind, a.V, a.R, a.C, a.sino, which);
+    const auto launch = [&](int v0, int V) {
+        const int64_t nb = LPL == 1 ? fwd_blocks(tR, tC, V) : (int64_t)tR * tC * V * LPL;
+        hipLaunchKernelGGL((project_kernel<n, LPL, WIDE>), dim3((unsigned)nb), dim3(256), 0, st, cz, cx, a.N[0],
+                           a.N[1], a.N[2], a.geom + 12 * (int64_t)v0, a.kind, V, a.R, a.C,
+                           a.sino + (int64_t)v0 * a.R * a.C, which, fwd_views(V));
+    };
+    if (LPL == 1) fwd_in_pieces(tR, tC, a.V, launch);
+    else launch(0, a.V);
 }
 
 template <int n>
@@ -1174,7 +1179,7 @@ static hipError_t launch_project_n(const LaunchArgs &a, hipStream_t st) {
     const int64_t Sx = a.N[0] + 2 * P, Sy = a.N[1] + 2 * P, Sz = a.N[2] + 2 * P, padded = Sx * Sy * Sz;
     if (!a.scratch || a.scratch_floats < padded) return hipErrorInvalidValue;
     const int64_t zb = ((Sx + PAD_T - 1) / PAD_T) * ((Sz + PAD_T - 1) / PAD_T) * Sy;
-    if (zb > INT32_MAX) return hipErrorInvalidValue;
+    if (zb > INT32_MAX || !fwd_launch_views((a.R + 15) / 16, (a.C + 15) / 16, a.V)) return hipErrorInvalidValue;
     const auto walk = [&](const float *cz, const float *cx, int which) {
         if (padded > (int64_t)1 << 30) launch_walk<n, 1, true>(a, cz, cx, which, st);
         else if ((int64_t)((a.R + 15) / 16) * ((a.C + 15) / 16) * a.V <= FWD_SHARED_TILES[n])

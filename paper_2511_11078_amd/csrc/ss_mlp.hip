@@ -22,7 +22,6 @@
 // weight image (built on the host from the blob) bakes this permutation
 // into the A operands, so activations never leave their lane.
 #include "ss_kernels.hpp"
-#include "ss_launch.hpp"
 
 #include <cstring>
 
@@ -563,10 +562,10 @@ __global__ void __launch_bounds__(256, 3) project_mlp_kernel(const float *__rest
 template <int n>
 __global__ void __launch_bounds__(256) project_pair_kernel(const float *__restrict__ c, int N0, int N1, int N2,
                                                            const float *__restrict__ geom, int kind, int V, int R,
-                                                           int C, float *__restrict__ y) {
+                                                           int C, float *__restrict__ y, int nv) {
     const int tR = (R + 15) / 16, tC = (C + 15) / 16;
     int v, tr, tc;
-    if (!fwd_block_tile(V, tR, tC, v, tr, tc)) return;  // padding slot: the whole block
+    if (!fwd_block_tile(V, nv, tR, tC, v, tr, tc)) return;  // padding slot: the whole block
     project_walk<n, true>(c, N0, N1, N2, geom, kind, V, R, C, nullptr, y, v, tr, tc);
 }
 
@@ -979,9 +978,12 @@ static hipError_t launch_backproject_mlp_n(const LaunchArgs &a, hipStream_t st) 
 template <int n>
 static hipError_t launch_project_pair_n(const LaunchArgs &a, hipStream_t st) {
     const int tR = (a.R + 15) / 16, tC = (a.C + 15) / 16;
-    hipLaunchKernelGGL(project_pair_kernel<n>, dim3((unsigned)fwd_blocks(tR, tC, a.V)), dim3(256), 0, st, a.coeffs,
-                       a.N[0], a.N[1], a.N[2], a.geom, a.kind, a.V, a.R, a.C, a.sino);
-    return hipGetLastError();
+    const bool fits = fwd_in_pieces(tR, tC, a.V, [&](int v0, int V) {
+        hipLaunchKernelGGL(project_pair_kernel<n>, dim3((unsigned)fwd_blocks(tR, tC, V)), dim3(256), 0, st, a.coeffs,
+                           a.N[0], a.N[1], a.N[2], a.geom + 12 * (int64_t)v0, a.kind, V, a.R, a.C,
+                           a.sino + (int64_t)v0 * a.R * a.C, fwd_views(V));
+    });
+    return fits ? hipGetLastError() : hipErrorInvalidValue;
 }
 
 template <int n>

@@ -2,6 +2,7 @@
 // quadrature and network kernels.
 #pragma once
 
+#include "ss_launch.hpp"
 #include "ss_math.hpp"
 
 namespace ss {
@@ -19,46 +20,15 @@ namespace ss {
 // A permutation of 0 .. nblocks - 1.
 // ---------------------------------------------------------------------------
 constexpr int XCD_RUN = 8;
-// XCD that takes the first of eight items of dealing round e
-__host__ __device__ inline int xcd_rotation(int e) { return e + e / 8 + e / 64; }
-__host__ __device__ inline int xcd_remap(int b, int nblocks) {
+constexpr int xcd_remap(int b, int nblocks) {
     if (b >= nblocks / (8 * XCD_RUN) * (8 * XCD_RUN)) return b;
     const int l = b / 8, e = l / XCD_RUN;
     return (e * 8 + ((b + xcd_rotation(e)) & 7)) * XCD_RUN + l % XCD_RUN;
 }
 
-// Forward launches: one 256-thread block per 16x16-pixel tile and view.
-// FT_GH x FT_GW tiles of up to FT_V consecutive views form an item, whose
-// blocks run on one XCD (hardware block h runs on XCD h % 8) and walk
-// neighbouring lines, which share coefficient lines in its L2.  The items go
-// to the XCDs eight at a time, each eight rotated against the last ones:
-// every XCD takes items from all over the detector and from all views, so
-// that they end together.  Before, whole groups of
-// tiles with all their views went to the XCDs in turn, and an XCD could get
-// the detector's edge or twice another's share: 200 views of 50 x 180 pixels
-// degree 2 3.65 -> 2.42 ms, degree 0 0.70 -> 0.47; 90 views of 111 x 147
-// degree 1 0.349 -> 0.284; cone_256 degree 3 150 -> 143, degree 2 71.9 -> 67.3.
-// Views per item 8, 16, 32: 2.42, 2.48, 2.79 and 0.284, 0.295, 0.302 ms.
-constexpr int FT_GH = 2, FT_GW = 2, FT_V = 8;
-__host__ __device__ inline int fwd_views(int V) { return V < FT_V ? V : FT_V; }
-__host__ __device__ inline int fwd_items(int tR, int tC, int V) {
-    return ((tR + FT_GH - 1) / FT_GH) * ((tC + FT_GW - 1) / FT_GW) * ((V + fwd_views(V) - 1) / fwd_views(V));
-}
-__host__ __device__ inline int64_t fwd_blocks(int tR, int tC, int V) {
-    return (int64_t)((fwd_items(tR, tC, V) + 7) / 8 * 8) * FT_GH * FT_GW * fwd_views(V);
-}
 // View and tile of this block; false for a padding slot (a whole block).
-__device__ __forceinline__ bool fwd_block_tile(int V, int tR, int tC, int &v, int &tr, int &tc) {
-    const int nv = fwd_views(V), per = FT_GH * FT_GW * nv, nch = (V + nv - 1) / nv;
-    const int l = blockIdx.x / 8, e = l / per, inner = l % per;
-    const int item = e * 8 + ((blockIdx.x + xcd_rotation(e)) & 7);
-    if (item >= fwd_items(tR, tC, V)) return false;
-    const int G = item / nch, q = inner / nv;
-    v = item % nch * nv + inner % nv;
-    const int gC = (tC + FT_GW - 1) / FT_GW;
-    tr = (G / gC) * FT_GH + q / FT_GW;
-    tc = (G % gC) * FT_GW + q % FT_GW;
-    return v < V && tr < tR && tc < tC;
+__device__ __forceinline__ bool fwd_block_tile(int V, int nv, int tR, int tC, int &v, int &tr, int &tc) {
+    return fwd_slot(blockIdx.x, V, nv, tR, tC, v, tr, tc);
 }
 
 struct ViewProj {    // detector coordinates of a world point (FP64 set-up)

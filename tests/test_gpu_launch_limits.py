@@ -1,6 +1,7 @@
 """Calls whose blocks do not fit one launch (HIP: fewer than 2^32 threads)."""
 import numpy as np
 import pytest
+import torch
 
 from paper_2511_11078_amd import synth
 from paper_2511_11078_amd.ops import Context
@@ -38,3 +39,27 @@ def test_network_forward_of_more_than_2_21_tiles():
     say(f"  rel-L2 {e:.3e}, non-zero {np.count_nonzero(want)} of {Cs}")
     assert np.count_nonzero(want) > 1000 and e <= 5e-4
     assert np.count_nonzero(got[:C - step * Cs]) == 0
+
+
+@pytest.mark.parametrize("form", ["quad", "pair"])
+def test_forward_of_more_than_2_24_slots(form):
+    """Two views of one row of 2^23 + 1 tiles: more than 2^24 blocks, so one
+    launch per view.  Equal to the views by themselves."""
+    C = 16 * 2**23 + 16
+    say(f"{form} forward, two views of one row of {C} columns")
+    vecs = []
+    for k, w in enumerate(([1.0, 0.3, 0.2], [0.2, -1.0, 0.4])):
+        w = np.asarray(w) / np.linalg.norm(w)
+        u, v = synth.detector_frame(w)
+        vecs.append(_row(w, u, v, 5.0e-7, C, 3.0 * k).vecs)
+    geom = synth.Geometry("parallel", 2, 1, C, np.concatenate(vecs))
+    c = to_gpu(np.random.default_rng(531).uniform(0.2, 1.0, (4, 5, 6)).astype(np.float32))
+    ctx = Context(1, form, 0)
+    out = torch.full((2, 1, C), float("nan"), device="cuda")
+    ctx.project(c, geom, out)
+    one = torch.empty((1, 1, C), device="cuda")
+    for k in range(2):
+        ctx.project(c, geom.subset_views(k, k + 1), one)
+        assert int(torch.count_nonzero(one)) > 1000
+        assert torch.equal(out[k], one[0])
+    ctx.close()
