@@ -326,6 +326,7 @@ static ss_status run_transform(ss_ctx *ctx, bool forward, const float *in, const
         if (ctx->form == SS_FORM_QUAD_FP32) {
             const int64_t one = ss::project_quad_scratch_floats(ctx->degree, a.N);
             a.walks_x = ctx->geom_walks_x;
+            a.spacing = ss::project_quad_spacing(geom->vecs, geom->kind);
             const int64_t all = one * ss::project_quad_copies(ctx->degree, a.N, a.walks_x);
             if (ss_status s = ensure_cells(ctx, one, all <= ctx->cell_limit ? all : one, st)) return s;
             a.scratch = ctx->cells.p;
@@ -401,6 +402,7 @@ ss_status ss_project_noalloc(int device, int degree, const float *d_coeffs, cons
     a.scratch = base + geom_floats;
     a.scratch_floats = ss::STATIC_SCRATCH_FLOATS - geom_floats;
     a.walks_x = ss::project_quad_walks_x(degree, geom->vecs, geom->n_views, (int)geom->kind);
+    a.spacing = ss::project_quad_spacing(geom->vecs, geom->kind);
     if ((e = ss::launch_project_quad(degree, a, st)) != hipSuccess) return hip_fail(e, "project launch");
     return SS_OK;
 }

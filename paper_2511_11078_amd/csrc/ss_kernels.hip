@@ -114,13 +114,28 @@ __host__ __device__ __forceinline__ ViewWalk view_walk(const float *__restrict__
 // ---------------------------------------------------------------------------
 
 // Launches of up to this many 16 x 16-pixel tiles share each line among four
-// lanes (project_kernel), by degree: all four walk the whole line, so the
-// shorter the integral the sooner that costs more than it gives.  Shared and
-// not, us: degree 0 490 tiles 60 and 62, 540 tiles 37 and 28, 960 tiles 207
-// and 148; degree 1 280 tiles 55 and 69, 384 tiles 202 and 192, 980 tiles 127
-// and 109; degree 2 700 tiles 167 and 249, 960 tiles 527 and 442; degree 3
-// 980 tiles 360 and 497, 1440 tiles 284 and 297, 1920 tiles 1780 and 1364.
-constexpr int64_t FWD_SHARED_TILES[4] = {512, 320, 768, 1536};
+// lanes (project_kernel), by degree and by the copy's size (up to
+// FWD_SHARED_FLOATS, and above): all four walk the whole line, so the
+// shorter the integral the sooner that costs more than it gives, and a wave of
+// sixteen lines reads more cache lines per integral, which counts once the
+// copy is large.  Shared and not, us, views of 1.5 N x 1.5 N pixels over N^3,
+// lines 2/3 of a coefficient apart:
+//   degree 0  N = 64 324 tiles 47 and 47, 504 59 and 46; 128 432 96 and 114, 576 120 and 89
+//   degree 1  N = 64 216 57 and 60, 324 66 and 59; 128 288 100 and 108, 576 167 and 112
+//   degree 2  N = 24 522 55 and 62, 954 86 and 74; 96 486 210 and 208, 648 252 and 191;
+//             160 225 167 and 223, 450 282 and 233
+//   degree 3  N = 48 525 190 and 207, 1150 382 and 371; 96 486 373 and 410, 648 463 and 396;
+//             160 225 324 and 395, 450 500 and 427; 256 1152 1742 and 1428
+// Lines further apart than FWD_SPARSE coefficients have few cache lines in
+// common within a wave of 64 either: what overlaps is the four lanes'
+// consecutive cells, and the launch may be larger (degree 3, 256^3, 16 views
+// of 96 x 96 pixels 3.4 apart, 576 tiles 1.14 and 2.37 ms; 384^3, one view of
+// 352 x 352 1.4 apart 1.08 and 1.24, 4 views of 256 x 256 1.9 apart 2.40 and
+// 2.29; 256^3, 4 views of 256 x 256 1.27 apart 1.48 and 1.17).
+constexpr int64_t FWD_SHARED_TILES[4][2] = {{330, 490}, {320, 320}, {560, 440}, {640, 440}};
+constexpr int64_t FWD_SHARED_FLOATS = (int64_t)1 << 21;
+constexpr int64_t FWD_SPARSE_TILES[4] = {512, 320, 768, 1536};
+constexpr float FWD_SPARSE = 1.3f;
 // Copies of up to this many floats (128 MiB) are walked in waves of 8 x 8
 // pixels instead of 16 x 4 at degrees 2 and 3.  Square waves idle less where
 // lines leave the volume (16 x 4 against 8 x 8: 128^3 with 192^2 pixels
@@ -222,7 +237,7 @@ __global__ void __launch_bounds__(256, n == 3 ? 3 : 4) project_kernel(const floa
         if (!fwd_block_tile(V, nv, tR, tC, v, tr, tc_)) return;  // padding slot
     } else {
         // four blocks per 16 x 16-pixel tile, tiles innermost: a launch this
-        // small spreads evenly, and its volume stays in every L2
+        // small spreads evenly over the chip
         const int t = blockIdx.x / LPL;
         part = blockIdx.x % LPL;
         tc_ = t % tC;
@@ -1180,10 +1195,11 @@ static hipError_t launch_project_n(const LaunchArgs &a, hipStream_t st) {
     if (!a.scratch || a.scratch_floats < padded) return hipErrorInvalidValue;
     const int64_t zb = ((Sx + PAD_T - 1) / PAD_T) * ((Sz + PAD_T - 1) / PAD_T) * Sy;
     if (zb > INT32_MAX || !fwd_launch_views((a.R + 15) / 16, (a.C + 15) / 16, a.V)) return hipErrorInvalidValue;
+    const int64_t tiles = (int64_t)((a.R + 15) / 16) * ((a.C + 15) / 16) * a.V;
+    const int64_t shared = a.spacing > FWD_SPARSE ? FWD_SPARSE_TILES[n] : FWD_SHARED_TILES[n][padded > FWD_SHARED_FLOATS];
     const auto walk = [&](const float *cz, const float *cx, int which) {
         if (padded > (int64_t)1 << 30) launch_walk<n, 1, true>(a, cz, cx, which, st);
-        else if ((int64_t)((a.R + 15) / 16) * ((a.C + 15) / 16) * a.V <= FWD_SHARED_TILES[n])
-            launch_walk<n, 4, false>(a, cz, cx, which, st);
+        else if (tiles <= shared) launch_walk<n, 4, false>(a, cz, cx, which, st);
         else launch_walk<n, 1, false>(a, cz, cx, which, st);
     };
     // the x-fastest copy, for the views that walk it, beside the z-fastest
@@ -1207,6 +1223,17 @@ static hipError_t launch_project_n(const LaunchArgs &a, hipStream_t st) {
 int64_t project_quad_scratch_floats(int degree, const int N[3]) {
     const int64_t P = degree + 1;
     return (N[0] + 2 * P) * (N[1] + 2 * P) * (N[2] + 2 * P);
+}
+
+float project_quad_spacing(const float *vec, int kind) {
+    const float *s = vec, *d0 = vec + 3, *u = vec + 6, *v = vec + 9;
+    const double cx = (double)u[1] * v[2] - (double)u[2] * v[1], cy = (double)u[2] * v[0] - (double)u[0] * v[2],
+                 cz = (double)u[0] * v[1] - (double)u[1] * v[0];
+    const auto norm = [](double x, double y, double z) { return sqrt(x * x + y * y + z * z); };
+    const double pitch = sqrt(norm(cx, cy, cz));
+    if (kind == 0) return (float)pitch;
+    const double sd = norm((double)d0[0] - s[0], (double)d0[1] - s[1], (double)d0[2] - s[2]);
+    return (float)(pitch * norm(s[0], s[1], s[2]) / sd);
 }
 
 int project_quad_copies(int degree, const int N[3], bool walks_x) {

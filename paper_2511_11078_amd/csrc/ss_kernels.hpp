@@ -37,6 +37,7 @@ struct LaunchArgs {
     float *scratch;        // quadrature forward: padded coefficients; adjoint: knot-cell table
     int64_t scratch_floats;
     bool walks_x;          // quadrature forward: some view walks the x-fastest copy
+    float spacing;         // quadrature forward: project_quad_spacing of the first view
 };
 
 // Default largest knot-cell table of the quadrature adjoint: 2^34 floats
@@ -52,6 +53,9 @@ int64_t project_quad_scratch_floats(int degree, const int N[3]);
 // Whether the forward walks any of these views (12 host floats each) in the
 // x-fastest copy.
 bool project_quad_walks_x(int degree, const float *vecs, int V, int kind);
+// Distance between a view's neighbouring lines (12 host floats) where they
+// pass the volume's centre: the root of a pixel's area, demagnified.
+float project_quad_spacing(const float *vec, int kind);
 // Copies of that size the forward uses if the scratch holds them (one is
 // enough; with two, one launch walks every view).
 int project_quad_copies(int degree, const int N[3], bool walks_x);

@@ -70,3 +70,20 @@ def test_one_copy_at_a_time(n, views):
     assert torch.equal(got, want)
     two.close()
     one.close()
+
+
+@pytest.mark.parametrize("n", [0, 2, 3])
+@pytest.mark.parametrize("pitch", [0.8, 1.9])
+def test_shared_lines_on_large_copies(n, pitch):
+    """140^3 (a copy above 2^21 floats), views of 4 x 5 tiles with dense and
+    with sparse lines: all 27 of them (540 tiles) and one at a time, on either
+    side of the shared-line rule where it has one between them.  Equal bits."""
+    say(f"shared lines on a large copy n={n} pitch={pitch}")
+    dims = (140, 139, 138)
+    geom = synth.parallel_geometry(synth.uniform_directions(27, seed=460), 60, 77, pitch=pitch)
+    c = torch.randn(dims[::-1], generator=torch.Generator("cuda").manual_seed(461), device="cuda")
+    ctx = Context(n, "quad", 0)
+    whole = ctx.project(c, geom)
+    parts = [ctx.project(c, geom.subset_views(v, v + 1)) for v in range(geom.n_views)]
+    assert torch.equal(whole, torch.cat(parts))
+    ctx.close()
