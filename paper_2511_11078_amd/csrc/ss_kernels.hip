@@ -466,7 +466,8 @@ __global__ void __launch_bounds__(256, n == 3 ? 3 : 4) project_kernel(const floa
 // Pass 1 blocks own GX x GY x GZ bricks of cells and take the views in
 // batches: as many consecutive views as fit half of the LDS line table (a
 // few hundred lines, up to 8 views; a view whose shadow is larger
-// than that is taken alone, in segments).  Per batch the block
+// than that is taken alone, in segments, each like a batch).  Per batch the
+// block
 //   - fills the half with the lines of each view's pixel rectangle (FP64
 //     set-up, anchor re-based at the brick centre), all threads taking part
 //     whatever the view,
@@ -483,7 +484,11 @@ __global__ void __launch_bounds__(256, n == 3 ? 3 : 4) project_kernel(const floa
 // queues: before a half is refilled, each wave runs as many rounds as its
 // lane with the most entries in that half needs, and lanes with fewer take
 // entries of the other half in the same rounds, so that the lanes of a wave,
-// whose candidate counts differ view by view, stay busy.
+// whose candidate counts differ view by view, stay busy.  (Segments that
+// emptied the queues each time took, at 60^3 with 24 parallel views of 4 x 4
+// pixels per coefficient, 1.20 instead of 0.90 ms at degree 0, 1.59 and 1.07,
+// 3.31 and 2.04, 5.60 and 3.69 at degree 3; only where a cell may have more
+// than 60 pixels in a row or column are they still.)
 //
 // What bounds it: VALU issue, 2.07 hits of about 440 instructions per (cell,
 // view) plus the set-up, at 0.34 wave instructions per SIMD per cycle (degree
@@ -505,12 +510,14 @@ __global__ void __launch_bounds__(256, n == 3 ? 3 : 4) project_kernel(const floa
 // coefficient layers.
 // ---------------------------------------------------------------------------
 constexpr int GX = 8, GY = 8, GZ = 4;
-constexpr int RUN_MAX = 64;           // columns and rows of a batched view's rectangle (6 bits each)
+constexpr int RUN_MAX = 64;           // most columns and rows of a run (6 bits each)
 constexpr int BV_CHUNK = 64;          // views whose brick constants are kept in LDS
 struct BrickViews {
     float nc[BV_CHUNK], nr[BV_CHUNK], dn[BV_CHUNK];  // centre's numerators and denominator
     float fc[BV_CHUNK], fr[BV_CHUNK];                // F of the columns and rows
-    int i0[BV_CHUNK], i1[BV_CHUNK], j0[BV_CHUNK], j1[BV_CHUNK];  // the brick's pixel rectangle
+    int i0[BV_CHUNK], j0[BV_CHUNK], w[BV_CHUNK], h[BV_CHUNK];  // the brick's pixel rectangle
+    int own[BV_CHUNK];  // its pixels; more than half the line table holds if the view goes alone, in segments: by one,
+                        // or by two if a cell may have more pixels than fit a run
 };
 // Line table (two halves) and occupancy per degree: the cubic kernel's
 // registers allow three waves per SIMD, so its table takes what LDS leaves
@@ -532,11 +539,9 @@ template <int n, bool SHARED> struct CellGather {
     // coefficients whose support meets a block's cells, and that count made even
     static constexpr int coeffs = (sx + n) * (sy + n) * (GZ + n), record = (coeffs + 1) / 2 * 2;
     using Part = std::conditional_t<n == 0, float, double>;  // a coefficient's part (degree 0: one FP32 entry)
-    static constexpr int seg_cols = SHARED ? 256 : n == 3 ? 376 : 224;  // lines of a segment of a larger view
     // wave priority while a block sets up a batch (0: the default throughout)
     static constexpr int setup_prio = n == 0 ? 0 : 2;
     static_assert(2 * half <= 1024, "a run's first entry has 10 bits");
-    static_assert(seg_cols <= half, "a segment fits a half");
 };
 // Launches of up to this many bricks, one per CU, share each cell's moments
 // (SHARED) at degrees 2 and 3: 32 views, degree 3, 225 bricks 164 -> 110 us,
@@ -699,7 +704,7 @@ __device__ __forceinline__ void pixel_rect(float cmin, float cmax, float rmin, f
 // bounded shadow: the whole detector, and unbounded F.
 // The cells are [x0, x0 + sx] x [y0, y0 + sy] of the brick's GX x GY (all of GZ).
 __device__ __forceinline__ void brick_view(const ViewProj &P, const double centre[3], int x0, int sx, int y0, int sy,
-                                           int R, int C, BrickViews &B, int s) {
+                                           int R, int C, int half, BrickViews &B, int s) {
     const float oc = 0.5f * (float)(C - 1) + P.gac_f, orow = 0.5f * (float)(R - 1) + P.gar_f;
     const double *c = centre;
     const float nc = (float)(fma(c[2], P.du_s[2], fma(c[1], P.du_s[1], c[0] * P.du_s[0])) - P.odu);
@@ -733,12 +738,21 @@ __device__ __forceinline__ void brick_view(const ViewProj &P, const double centr
     B.nc[s] = nc;
     B.nr[s] = nr;
     B.dn[s] = dn;
-    B.fc[s] = bad ? 3.0e38f : 0.5f * fmaxf(fc, gc);
-    B.fr[s] = bad ? 3.0e38f : 0.5f * fmaxf(fr, gr);
+    fc = bad ? 3.0e38f : 0.5f * fmaxf(fc, gc);
+    fr = bad ? 3.0e38f : 0.5f * fmaxf(fr, gr);
+    // whether every cell's pixels fit a run: those of a larger rectangle by
+    // the bound on the shadow where the brick comes nearest to the source
+    const float near = dn - 8.0f * P.hn_f;
+    const bool runs = (i1 - i0 < RUN_MAX && j1 - j0 < RUN_MAX) ||
+                      (near > 0.0f && fmaxf(fc, fr) <= 0.5f * (RUN_MAX - 4) * near);
+    B.fc[s] = fc;
+    B.fr[s] = fr;
     B.i0[s] = i0;
-    B.i1[s] = i1;
     B.j0[s] = j0;
-    B.j1[s] = j1;
+    B.w[s] = i1 - i0 + 1;
+    B.h[s] = j1 - j0 + 1;
+    const int lines = (i1 - i0 + 1) * (j1 - j0 + 1);  // 0 for a view that misses the detector
+    B.own[s] = !runs ? half + 2 : lines <= half ? lines : half + 1;
 }
 
 // Three (degree 3, at most 168 VGPRs) or four (lower degrees, 128) waves per
@@ -756,7 +770,7 @@ backproject_cells_kernel(const float *__restrict__ y, int N0, int N1, int N2, co
     constexpr int THREADS = CellGather<n, SHARED>::threads, SX = CellGather<n, SHARED>::sx, SY = CellGather<n, SHARED>::sy;
     constexpr int BATCH_VIEWS = CellGather<n, SHARED>::batch, RING = 2 * BATCH_VIEWS;  // queued runs per thread
     constexpr int MOMENTS = SHARED ? NB * NB : NB * NB * NB;  // of a thread
-    constexpr int HALF = CellGather<n, SHARED>::half, SEG_COLS = CellGather<n, SHARED>::seg_cols;
+    constexpr int HALF = CellGather<n, SHARED>::half;
     // A batch's set-up (records, line table, queueing) is short dependent
     // chains ending in a barrier; the integration is long runs of
     // independent FMAs.  Raising a wave's priority for the set-up lets each
@@ -849,16 +863,15 @@ backproject_cells_kernel(const float *__restrict__ y, int N0, int N1, int N2, co
             // old ones: they precede the last barrier)
             rec0 = v;
             rec1 = min(v + BV_CHUNK, V);
-            if (tid < rec1 - rec0) brick_view(vps[rec0 + tid], centre, ox, SX, oy, SY, R, C, bv, tid);
+            if (tid < rec1 - rec0) brick_view(vps[rec0 + tid], centre, ox, SX, oy, SY, R, C, HALF, bv, tid);
             __syncthreads();
         }
         // lane l < BATCH_VIEWS holds view v + l: its pixel rectangle, and the
         // lines of the views before it
         const int lv = max(min(v - rec0 + (lane & (BATCH_VIEWS - 1)), rec1 - rec0 - 1), 0);
         int vi0 = bv.i0[lv], vj0 = bv.j0[lv];
-        int W = bv.i1[lv] - vi0 + 1, H = bv.j1[lv] - vj0 + 1;
-        const bool over = W > RUN_MAX || H > RUN_MAX || W * H > HALF;
-        const int own = over ? HALF + 1 : W * H;  // 0 for a view that misses the detector
+        int W = bv.w[lv], H = bv.h[lv];
+        const int own = bv.own[lv];
         int upto = own;                           // inclusive sum over lanes 0 .. l
 #pragma unroll
         for (int m = 1; m < BATCH_VIEWS; m <<= 1) {
@@ -868,12 +881,14 @@ backproject_cells_kernel(const float *__restrict__ y, int N0, int N1, int N2, co
         const bool fits = lane < BATCH_VIEWS && v + lane < V && upto <= HALF;
         int K = __popcll(__ballot(fits));  // views in this batch (the sums do not decrease)
         // a view too large for a batch comes alone, in segments of whole rows
-        // (of columns, for a row wider than SEG_COLS)
-        const bool done = v >= V, large = K == 0;
+        // (of columns, for a row wider than that); direct: not queued
+        const bool done = v >= V, large = K == 0, direct = __builtin_amdgcn_readlane(own, 0) > HALF + 1;
         // every wave retires its entries of the half that is refilled; before
-        // a segment and at the end, all of them
+        // a segment that does not go through the queues and at the end, all
         prio_integrate();
-        drain(large ? INT32_MAX : wave_max(nolder));
+        int rounds = wave_max(nolder);
+        if (done || direct) rounds = INT32_MAX;
+        drain(rounds);
         if (done) break;
         if (batch >= 2) __syncthreads();
         prio_setup();
@@ -883,7 +898,7 @@ backproject_cells_kernel(const float *__restrict__ y, int N0, int N1, int N2, co
         const int vb = v;
         if (large) {
             const int BW = __builtin_amdgcn_readlane(W, 0), BH = __builtin_amdgcn_readlane(H, 0);
-            const int scols = min(BW, SEG_COLS), srows = SEG_COLS / scols;
+            const int scols = min(BW, HALF), srows = HALF / scols;
             vi0 += si;
             vj0 += sj;
             W = min(scols, BW - si);
@@ -940,7 +955,7 @@ backproject_cells_kernel(const float *__restrict__ y, int N0, int N1, int N2, co
             if (mine && fi0 <= fi1 && fj0 <= fj1) {
                 const int ni = (int)(fi1 - fi0), nj = (int)(fj1 - fj0);  // columns and rows, less 1
                 const int first = half + __builtin_amdgcn_readlane(tb, k) + (int)fmaf(fj0, (float)w, fi0);
-                if (large) {  // the queue is empty: straight to the registers
+                if (direct) {  // the queue is empty: straight to the registers
                     ent = first;
                     cols = cleft = ni + 1;
                     rleft = nj + 1;

@@ -109,3 +109,28 @@ def test_parts_of_blocks(n, dims, limit):
     e = rel_l2(got.ravel(), np.asarray(want).ravel())
     say(f"  rel-L2 {e:.3e}")
     assert e <= (1e-5 if n > 0 else 1e-4)
+
+
+FINE = {
+    # name: (views, rows, cols, pitches, detector shift)
+    "rows_wider_than_64_in_batches": (9, 1, 410, [0.12, 0.9, 0.06], 0.0),
+    "columns_taller_than_64_in_batches": (9, 270, 1, [0.1, 0.2], 0.0),
+    "queued_segments": (7, 70, 90, [0.25, 0.16], 0.0),
+    # a cell's pixels in a row: 61 still go into a run, the next pitch not
+    "edge_of_a_run": (8, 5, 700, [0.03, 0.025, 0.02, 1.0, 0.012], 0.0),
+    "queued_and_direct_in_turn": (9, 33, 120, [0.2, 0.015, 0.05], 0.0),
+}
+
+
+@pytest.mark.parametrize("n", [0, 1, 2, 3])
+@pytest.mark.parametrize("case", list(FINE))
+def test_fine_pixels(case, n):
+    """Views whose rectangle on a brick is larger than the line table's half,
+    or than a run of the queue, before and after views that fit."""
+    views, R, C, pitches, shift = FINE[case]
+    say(f"cell batches, fine pixels {case} n={n}")
+    geom = synth.Geometry("parallel", views, R, C, _tilted(views, pitches, shift, seed=330))
+    dims = VOLUMES["small"] if case != "queued_segments" else (19, 18, 33)
+    e = _adjoint_error(n, geom, dims, 331)
+    say(f"  rel-L2 {e:.3e}")
+    assert e <= (1e-5 if n > 0 else 1e-4)
