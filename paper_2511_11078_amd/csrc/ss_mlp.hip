@@ -415,13 +415,14 @@ template <int n, bool EXACT, int LINES = 64>
 __device__ __forceinline__ void project_walk(const float *__restrict__ c, int N0, int N1, int N2,
                                              const float *__restrict__ geom, int kind, int V, int R, int C,
                                              const MlpImage *Wt, float *__restrict__ y, int v, int tr, int tc,
-                                             int part = 0, FwdPairBuf *fbuf = nullptr, float *accw = nullptr) {
+                                             int part = 0, int lw = 3, int pc = 2, FwdPairBuf *fbuf = nullptr,
+                                             float *accw = nullptr) {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    // LINES pixels of the 16 x 16 tile, PW in a row
-    constexpr int PW = LINES >= 32 ? 8 : 4, PER_ROW = 16 / PW, GROUPS = 64 / LINES;
+    // a patch of LINES pixels of the 16 x 16 tile, 2^lw in a row; pc patches side by side
+    constexpr int GROUPS = 64 / LINES;
     const int patch = EXACT ? wave : part, line = lane % LINES;
-    const int j = tr * 16 + patch / PER_ROW * (LINES / PW) + line / PW;
-    const int i = tc * 16 + patch % PER_ROW * PW + line % PW;
+    const int j = tr * 16 + patch / pc * (LINES >> lw) + (line >> lw);
+    const int i = tc * 16 + (patch % pc << lw) + (line & ((1 << lw) - 1));
     const bool pix = v < V && j < R && i < C;
     const int N[3] = {N0, N1, N2};
     const double centre[3] = {0.0, 0.0, 0.0};
@@ -544,19 +545,19 @@ template <int n, int LINES>
 __global__ void __launch_bounds__(256, 3) project_mlp_kernel(const float *__restrict__ c, int N0, int N1, int N2,
                                                           const float *__restrict__ geom, int kind, int V, int R,
                                                           int C, const MlpImage *__restrict__ img,
-                                                          float *__restrict__ y, int t0) {
+                                                          float *__restrict__ y, int t0, int lw, int pc,
+                                                          int parts) {
     __shared__ MlpImage Wt;
     __shared__ FwdPairBuf fbuf[4];  // one ring per wave of the 256-thread block
     __shared__ float accw[256];
-    // 256 / LINES blocks per 16 x 16-pixel tile, views outermost; the
-    // launch's first tile is t0
+    // `parts` blocks per 16 x 16-pixel tile, views outermost; the launch's
+    // first tile is t0
     const int tR = (R + 15) / 16, tC = (C + 15) / 16;
-    constexpr int PARTS = 256 / LINES;
-    const int part = blockIdx.x % PARTS, t = t0 + (int)(blockIdx.x / PARTS), tc = t % tC, tr = (t / tC) % tR;
+    const int part = blockIdx.x % parts, t = t0 + (int)(blockIdx.x / parts), tc = t % tC, tr = (t / tC) % tR;
     const int v = t / (tC * tR);
     load_image(Wt, img);
     __syncthreads();
-    project_walk<n, false, LINES>(c, N0, N1, N2, geom, kind, V, R, C, &Wt, y, v, tr, tc, part, fbuf, accw);
+    project_walk<n, false, LINES>(c, N0, N1, N2, geom, kind, V, R, C, &Wt, y, v, tr, tc, part, lw, pc, fbuf, accw);
 }
 
 template <int n>
@@ -939,18 +940,27 @@ __global__ void __launch_bounds__(64) footprint_mlp_kernel(const float *__restri
 template <int n, int LINES>
 static void launch_project_mlp_lines(const LaunchArgs &a, hipStream_t st) {
     const int64_t tiles = (int64_t)((a.R + 15) / 16) * ((a.C + 15) / 16) * a.V;
-    constexpr int PARTS = 256 / LINES;
-    in_pieces(tiles, 256 * PARTS, [&](int64_t t0, int64_t count) {
-        hipLaunchKernelGGL((project_mlp_kernel<n, LINES>), dim3((unsigned)(count * PARTS)), dim3(256), 0, st, a.coeffs,
+    // patches as nearly square as the detector has rows and columns for, and
+    // only those that a detector of less than a tile's rows or columns has:
+    // of a single row's 16 patches of 4 x 4 pixels four had a line, and their
+    // blocks went to four of the eight XCDs (40 views of 1 x 384 over 256 x
+    // 256 x 1, degree 3: 5.8 and 2.2 ms)
+    int lw = LINES >= 32 ? 3 : 2;
+    while (lw < 4 && (LINES >> lw) > a.R) ++lw;
+    while (lw > 0 && (1 << lw) > a.C && (LINES >> (lw - 1)) <= 16) --lw;
+    const auto patches = [](int pixels, int side) { return (std::min(pixels, 16) - 1) / side + 1; };
+    const int pc = patches(a.C, 1 << lw), parts = patches(a.R, LINES >> lw) * pc;
+    in_pieces(tiles, 256 * parts, [&](int64_t t0, int64_t count) {
+        hipLaunchKernelGGL((project_mlp_kernel<n, LINES>), dim3((unsigned)(count * parts)), dim3(256), 0, st, a.coeffs,
                            a.N[0], a.N[1], a.N[2], a.geom, a.kind, a.V, a.R, a.C, (const MlpImage *)a.mlp, a.sino,
-                           (int)t0);
+                           (int)t0, lw, pc, parts);
     });
 }
 
 template <int n>
 static hipError_t launch_project_mlp_n(const LaunchArgs &a, hipStream_t st) {
     const int64_t tiles = (int64_t)((a.R + 15) / 16) * ((a.C + 15) / 16) * a.V;
-    if (tiles <= SMALL_TILES) launch_project_mlp_lines<n, 16>(a, st);
+    if (tiles <= SMALL_TILES || a.R == 1 || a.C == 1) launch_project_mlp_lines<n, 16>(a, st);
     else launch_project_mlp_lines<n, 32>(a, st);
     return hipGetLastError();
 }

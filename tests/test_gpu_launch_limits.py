@@ -16,15 +16,15 @@ def _row(w, u, v, pitch, C, centre):
     return synth.Geometry("parallel", 1, 1, C, np.concatenate([w, centre * u, pitch * u, v])[None].astype(np.float32))
 
 
-def test_network_forward_of_more_than_2_21_tiles():
-    """One row of 16 x 2^21 + 40 columns is three tiles more than one launch of
-    eight blocks a tile takes.  The volume lies before its last 400,000
-    columns: those are compared with a row of every 64th of them, the others
-    see nothing.  The rows' FP32 centres and pitches put a line up to 6e-5 of
-    a coefficient's width apart (335 of them times 2^-24, twice, and the
-    centre's own rounding); sums change by no more than their own size per
-    such width, and 5e-4 leaves eight times that."""
-    C, Cs, step, pitch = 16 * 2**21 + 40, 8192, 64, 2.0e-5
+def test_network_forward_of_more_than_one_launch():
+    """One row of 16 x 2^24 + 40 columns, a block of 256 threads per 16 of
+    them, is four blocks more than one launch takes.  The volume lies before
+    its last 4 million columns: those are compared with a row of every 512th
+    of them, the others see nothing.  The rows' FP32 centres and pitches put a
+    line up to 6e-5 of a coefficient's width apart (335 of them times 2^-24,
+    twice, and the centre's own rounding); sums change by no more than their
+    own size per such width, and 5e-4 leaves eight times that."""
+    C, Cs, step, pitch = 16 * 2**24 + 40, 8192, 512, 2.5e-6
     say(f"network forward, one row of {C} columns")
     w = np.array([1.0, 0.3, 0.2]) / np.linalg.norm([1.0, 0.3, 0.2])
     u, v = synth.detector_frame(w)
@@ -33,12 +33,12 @@ def test_network_forward_of_more_than_2_21_tiles():
     few = _row(w, u, v, pitch * step, Cs, centre + pitch * ((C - 1) / 2 - step * (Cs - 1) / 2))
     c = to_gpu(np.random.default_rng(530).uniform(0.2, 1.0, (4, 5, 6)).astype(np.float32))
     ctx = Context(1, "mlp", 0)
-    got, want = to_np(ctx.project(c, wide)).ravel(), to_np(ctx.project(c, few)).ravel()
+    got, want = ctx.project(c, wide).flatten(), to_np(ctx.project(c, few)).ravel()
     ctx.close()
-    e = rel_l2(got[C - 1 - step * (Cs - 1)::step], want)
+    e = rel_l2(to_np(got[C - 1 - step * (Cs - 1)::step]), want)
     say(f"  rel-L2 {e:.3e}, non-zero {np.count_nonzero(want)} of {Cs}")
     assert np.count_nonzero(want) > 1000 and e <= 5e-4
-    assert np.count_nonzero(got[:C - step * Cs]) == 0
+    assert int(torch.count_nonzero(got[:C - step * Cs])) == 0
 
 
 @pytest.mark.parametrize("form", ["quad", "pair"])

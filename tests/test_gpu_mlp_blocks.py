@@ -66,3 +66,35 @@ def test_line_sharing_rules_agree():
     e = rel_l2(whole, np.concatenate(parts))
     say(f"  rel-L2 {e:.3e}")
     assert np.abs(whole).max() > 0 and e <= 2e-5
+
+
+THIN = {
+    # name: (dims, views, rows, cols, pitch); patches of 16 or 32 lines of a 16 x 16 tile
+    "one_row": ((9, 8, 7), 3, 1, 37, 0.4),
+    "one_column": ((9, 8, 7), 3, 37, 1, 0.4),
+    "two_rows": ((6, 5, 7), 3, 2, 19, 0.6),
+    "two_columns": ((6, 5, 7), 3, 21, 2, 0.6),
+    "three_by_three": ((6, 5, 7), 3, 3, 3, 1.5),
+    "many_views_of_one_row": ((4, 3, 5), 1030, 1, 5, 1.0),     # more than 1024 tiles
+    "many_views_of_two_rows": ((4, 3, 5), 1030, 2, 3, 1.0),    # 32 lines: 2 x 16
+    "many_views_of_three_columns": ((4, 3, 5), 1030, 5, 3, 1.0),
+    "many_views_of_nine_rows": ((4, 3, 5), 520, 9, 17, 0.5),
+}
+
+
+@pytest.mark.parametrize("case", list(THIN))
+def test_patches_of_thin_detectors(case):
+    """Detectors of fewer rows or columns than a patch of lines."""
+    dims, views, R, C, pitch = THIN[case]
+    say(f"network patches {case} {dims}")
+    with open(default_weights(3), "rb") as fh:
+        blob = fn.parse_blob(fh.read())
+    geom = tilted_parallel(views, R, C, seed=520, pitch=pitch)
+    c = np.random.default_rng(521).uniform(0.2, 1.0, dims[::-1]).astype(np.float32)
+    ctx = Context(3, "mlp", 0)
+    got = to_np(ctx.project(to_gpu(c), geom))
+    ctx.close()
+    want = _pairs_reference(blob, 3, c, geom)
+    e = rel_l2(got, want)
+    say(f"  rel-L2 {e:.3e}")
+    assert np.abs(want).max() > 0 and e <= 2e-5
