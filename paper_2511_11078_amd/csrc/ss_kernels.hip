@@ -1059,13 +1059,23 @@ backproject_cells_kernel(const float *__restrict__ y, int N0, int N1, int N2, co
         for (int r = 0; r < PER; ++r) {
             const int e = tid + r * THREADS, i = e % EX, j = (e / EX) % EY, z = e / (EX * EY) - a3;
             if (e >= NC || z < 0 || z >= GZ) continue;
-            for (int a2 = 0; a2 < NB; ++a2) {
-                if (j - a2 < 0 || j - a2 >= SY) continue;
-                const float *row = x + ((SHARED ? a3 * NB * NB : 0) + a2 * NB) * CELLS + (z * SY + j - a2) * SX + i;
+            // all loads at once; a cell outside the block adds 0 (branches
+            // around each load cost a call of one view over 33 x 31 x 40
+            // 24.5 instead of 21.9 us at degree 3, 16.5 and 14.8 at degree 2)
+            const float *at = x + (SHARED ? a3 * NB * NB : 0) * CELLS;
+            float t[NB][NB];
 #pragma unroll
-                for (int a1 = 0; a1 < NB; ++a1)
-                    if (i - a1 >= 0 && i - a1 < SX) sum[r] += (double)row[a1 * CELLS - a1];
-            }
+            for (int a2 = 0; a2 < NB; ++a2)
+#pragma unroll
+                for (int a1 = 0; a1 < NB; ++a1) {
+                    const bool in = (unsigned)(j - a2) < (unsigned)SY && (unsigned)(i - a1) < (unsigned)SX;
+                    const float v = at[in ? (a2 * NB + a1) * CELLS + (z * SY + j - a2) * SX + i - a1 : 0];
+                    t[a2][a1] = in ? v : 0.0f;
+                }
+#pragma unroll
+            for (int a2 = 0; a2 < NB; ++a2)
+#pragma unroll
+                for (int a1 = 0; a1 < NB; ++a1) sum[r] += (double)t[a2][a1];
         }
     }
     const int qx = SHARED ? 2 * bx + (part & 1) : bx, qy = SHARED ? 2 * by + (part >> 1) : by;
@@ -1094,12 +1104,25 @@ __global__ void __launch_bounds__(256) cells_to_coeffs_kernel(const typename Cel
     // cells of the support, relative to the volume's (the chunk's) first:
     // k0 .. k0 + n, k1 .. k1 + n, z .. z + n
     const int z = k2 - qoff - mz0 - n;
+    // one or two blocks per axis: all loads at once, a block that is not there
+    // adds 0 (one after the other, each waited for: one view over 33 x 31 x 40
+    // 21.9 instead of 20.1 us at degree 3, 14.8 and 13.4 at degree 2)
+    static_assert(n < G::sx && n < G::sy && n < GZ + 1, "at most two blocks per axis");
+    const int bx0 = k0 / G::sx, by0 = k1 / G::sy, bz0 = z / GZ;
+    const bool mx = (k0 + n) / G::sx != bx0, my = (k1 + n) / G::sy != by0, mz = (z + n) / GZ != bz0;
+    typename G::Part t[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        const int qx = q & 1, qy = (q >> 1) & 1, qz = q >> 2;
+        const bool in = (!qx || mx) && (!qy || my) && (!qz || mz);
+        const int bx = bx0 + (in ? qx : 0), by = by0 + (in ? qy : 0), bz = bz0 + (in ? qz : 0);
+        const auto v = T[(((int64_t)bz * nqy + by) * nqx + bx) * G::record +
+                         ((z + n - bz * GZ) * (G::sy + n) + k1 + n - by * G::sy) * (G::sx + n) + k0 + n - bx * G::sx];
+        t[q] = in ? v : 0;
+    }
     double s = 0.0;
-    for (int bz = z / GZ; bz <= (z + n) / GZ; ++bz)
-        for (int by = k1 / G::sy; by <= (k1 + n) / G::sy; ++by)
-            for (int bx = k0 / G::sx; bx <= (k0 + n) / G::sx; ++bx)
-                s += T[(((int64_t)bz * nqy + by) * nqx + bx) * G::record +
-                       ((z + n - bz * GZ) * (G::sy + n) + k1 + n - by * G::sy) * (G::sx + n) + k0 + n - bx * G::sx];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) s += t[q];
     c[(int64_t)k2 * per + rem] = (float)s;
 }
 

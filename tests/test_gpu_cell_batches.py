@@ -134,3 +134,40 @@ def test_fine_pixels(case, n):
     e = _adjoint_error(n, geom, dims, 331)
     say(f"  rel-L2 {e:.3e}")
     assert e <= (1e-5 if n > 0 else 1e-4)
+
+
+@pytest.mark.parametrize("n", [0, 1, 2, 3])
+@pytest.mark.parametrize("dims", [(1, 2, 3), (5, 13, 4), (9, 8, 17), (52, 44, 61)])
+def test_parts_are_summed_once(n, dims):
+    """The sums over a block's cells and over the blocks of a coefficient load
+    every part they might need and add 0 for those that are not there: every
+    coefficient of volumes around the blocks' edges against the oracle, and
+    non-finite parts stay where they belong."""
+    say(f"parts of blocks n={n} {dims}")
+    geom = synth.Geometry("parallel", 3, 30, 31, _tilted(3, [max(dims) / 20.0], 0.0, seed=350))
+    y = np.random.default_rng(351).standard_normal((3, 30, 31)).astype(np.float32)
+    ctx = Context(n, "quad", 0)
+    got = to_np(ctx.backproject(to_gpu(y), geom, dims))
+    want = oracle.backproject_subset(y, geom, dims, n)
+    assert np.abs(want).max() > 0
+    e = rel_l2(got, want)
+    say(f"  rel-L2 {e:.3e}")
+    assert e <= (1e-5 if n > 0 else 1e-4)
+    # one infinite pixel: only coefficients that its line meets (by the
+    # oracle) may differ from the finite result
+    y[1, 15, 16] = 0.0
+    base = to_np(ctx.backproject(to_gpu(y), geom, dims))
+    y[1, 15, 16] = np.inf
+    inf = to_np(ctx.backproject(to_gpu(y), geom, dims))
+    ctx.close()
+    one = np.zeros_like(y)
+    one[1, 15, 16] = 1.0
+    met = oracle.backproject_subset(one, geom, dims, n).reshape(got.shape) != 0
+    h = np.pad(met, n + 1)
+    near = np.zeros_like(met)
+    for dz in range(2 * n + 3):
+        for dy in range(2 * n + 3):
+            for dx in range(2 * n + 3):
+                near |= h[dz:dz + met.shape[0], dy:dy + met.shape[1], dx:dx + met.shape[2]]
+    assert np.array_equal(inf[~near], base[~near])
+    assert met.any() and not np.isfinite(inf[met]).all()
