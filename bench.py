@@ -72,7 +72,7 @@ TRAFFIC_SHA256 = "d9a458204c8500079694fe034760c0b05c36d5d13dfced18e53fae15168995
 TRAFFIC_BYTES = {  # (kernel, degree) -> (read bytes, written bytes) per application, cone_256
     ("pad_volume_kernel", 3): (2.0 * 36888 * 1024, 1.0 * 71874 * 1024),
     ("pad_volume_zfast_kernel", 3): (2.0 * 65563 * 1024, 1.0 * 72250 * 1024),
-    ("pad_volume_yfast_kernel", 3): (0.0, 0.0),  # a y-fastest copy is no longer made
+    ("pad_volume_yfast_kernel", 3): (0.0, 0.0),  # no such kernel: the other copy is z fastest
     ("project_kernel", 3): (2.0 * 4315956 * 1024, 1.0 * 281855 * 1024),
     ("backproject_cells_kernel", 3): (2.0 * 3169364 * 1024, 1.0 * 468950 * 1024),
     ("cells_to_coeffs_kernel", 3): (2.0 * 521261 * 1024, 1.0 * 65536 * 1024),

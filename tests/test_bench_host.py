@@ -53,3 +53,23 @@ def test_several_gpus_are_refused_with_a_message():
                        text=True, timeout=120, cwd=ROOT)
     assert r.returncode == 2
     assert "one GPU" in (r.stdout + r.stderr)
+
+
+def test_traffic_of_the_forward_as_the_benchmark_sums_it():
+    # cone_256's views walk the z-fastest copy; a view along z, the other one
+    for n in (3, 0):
+        for k in ("pad_volume_zfast_kernel", "pad_volume_kernel"):
+            r, w = bench.TRAFFIC_BYTES[(k, n)]
+            # each reads the 256^3 volume and writes a copy padded by n + 1
+            # (all but lines still in the caches when the counters were read)
+            assert 4 * 256 ** 3 <= r < 2.5 * 4 * 256 ** 3 and w >= 0.999 * 4 * (256 + 2 * (n + 1)) ** 3
+            assert bench.L2_FILL_BYTES[(k, n)] >= 4 * 256 ** 3
+        both = bench.measured_traffic(["pad_volume_zfast_kernel", "project_kernel"], n, "cone_256")
+        assert both == sum(bench.TRAFFIC_BYTES[("pad_volume_zfast_kernel", n)]) + sum(
+            bench.TRAFFIC_BYTES[("project_kernel", n)])
+    # a kernel that no source defines has no traffic of its own
+    src = os.path.join(ROOT, "paper_2511_11078_amd", "csrc", "ss_kernels.hip")
+    with open(src) as fh:
+        text = fh.read()
+    for (k, n), rw in list(bench.TRAFFIC_BYTES.items()):
+        assert (f"{k}(" in text) == (sum(rw) > 0)
