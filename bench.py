@@ -68,18 +68,18 @@ MLP_TRANS_PER_PAIR = 2 * 4 * 64   # SiLU of 4 x 64 hidden units: one exp and one
 # were measured on (SHA-256 over QUAD_SOURCES); otherwise reported as null.
 QUAD_SOURCES = ["csrc/ss_kernels.hip", "csrc/ss_math.hpp", "csrc/ss_traverse.hpp", "csrc/ss_kernels.hpp",
                 "csrc/ss_launch.hpp"]
-TRAFFIC_SHA256 = "d9a458204c8500079694fe034760c0b05c36d5d13dfced18e53fae1516899512"
+TRAFFIC_SHA256 = "d8293e01769f418f3722c284b3ba9588d8bf11f71f94146a3912128d442c2b3d"
 TRAFFIC_BYTES = {  # (kernel, degree) -> (read bytes, written bytes) per application, cone_256
     ("pad_volume_kernel", 3): (2.0 * 36888 * 1024, 1.0 * 71874 * 1024),
-    ("pad_volume_zfast_kernel", 3): (2.0 * 65563 * 1024, 1.0 * 72250 * 1024),
+    ("pad_volume_zfast_kernel", 3): (2.0 * 65559 * 1024, 1.0 * 72251 * 1024),
     ("pad_volume_yfast_kernel", 3): (0.0, 0.0),  # no such kernel: the other copy is z fastest
-    ("project_kernel", 3): (2.0 * 4315956 * 1024, 1.0 * 281855 * 1024),
-    ("backproject_cells_kernel", 3): (2.0 * 3169364 * 1024, 1.0 * 468950 * 1024),
+    ("project_kernel", 3): (2.0 * 4318666 * 1024, 1.0 * 281880 * 1024),
+    ("backproject_cells_kernel", 3): (2.0 * 3169822 * 1024, 1.0 * 468950 * 1024),
     ("cells_to_coeffs_kernel", 3): (2.0 * 521261 * 1024, 1.0 * 65536 * 1024),
-    ("pad_volume_zfast_kernel", 0): (2.0 * 65562 * 1024, 1.0 * 79979 * 1024),
+    ("pad_volume_zfast_kernel", 0): (2.0 * 65557 * 1024, 1.0 * 72242 * 1024),
     ("pad_volume_kernel", 0): (2.0 * 36889 * 1024, 1.0 * 67084 * 1024),
-    ("project_kernel", 0): (2.0 * 3471377 * 1024, 1.0 * 288477 * 1024),
-    ("backproject_cells_kernel", 0): (2.0 * 3136923 * 1024, 1.0 * 65536 * 1024),
+    ("project_kernel", 0): (2.0 * 3473543 * 1024, 1.0 * 289296 * 1024),
+    ("backproject_cells_kernel", 0): (2.0 * 3136521 * 1024, 1.0 * 65536 * 1024),
     ("cells_to_coeffs_kernel", 0): (2.0 * 131092 * 1024, 1.0 * 65536 * 1024),
 }
 
@@ -93,13 +93,13 @@ L2_FILL_BYTES = {  # (kernel, degree) -> bytes per application, cone_256
     ("pad_volume_kernel", 3): 128.0 * 589824,
     ("pad_volume_zfast_kernel", 3): 128.0 * 1048576,
     ("pad_volume_yfast_kernel", 3): 0.0,
-    ("project_kernel", 3): 128.0 * 11985253001,
-    ("backproject_cells_kernel", 3): 128.0 * 270073683,
-    ("cells_to_coeffs_kernel", 3): 128.0 * 9015397,
+    ("project_kernel", 3): 128.0 * 11981560029,
+    ("backproject_cells_kernel", 3): 128.0 * 270076271,
+    ("cells_to_coeffs_kernel", 3): 128.0 * 9010682,
     ("pad_volume_zfast_kernel", 0): 128.0 * 1048576,
     ("pad_volume_kernel", 0): 128.0 * 589824,
-    ("project_kernel", 0): 128.0 * 2096983848,
-    ("backproject_cells_kernel", 0): 128.0 * 250981259,
+    ("project_kernel", 0): 128.0 * 2096358948,
+    ("backproject_cells_kernel", 0): 128.0 * 250986622,
     ("cells_to_coeffs_kernel", 0): 128.0 * 2097152,
 }
 PEAK_L2_TBS = 8 * 16 * 128 * 2.4e9 / 1e12

@@ -491,14 +491,14 @@ __global__ void __launch_bounds__(256, n == 3 ? 3 : 4) project_kernel(const floa
 // than 60 pixels in a row or column are they still.)
 //
 // What bounds it: VALU issue, 2.07 hits of about 440 instructions per (cell,
-// view) plus the set-up, at 0.34 wave instructions per SIMD per cycle (degree
+// view) plus the set-up, at 0.36 wave instructions per SIMD per cycle (degree
 // 3; independent FMAs reach 0.41).  With a corner table, a barrier and a
 // partly filled line set-up per view instead of per batch, and a queue of
-// single entries, cone_256 took 187.5 ms at degree 3 and 70.9 ms at degree 0;
-// with the batches 156 and 50.6 ms (1.43e11 -> 1.32e11 and 3.79e10 -> 2.75e10
-// VALU instructions, half the scalar ones), and with the plain slab test for
-// tables without axis-parallel lines 153 and 46.1 ms; bit for bit the same
-// sums.
+// single entries, cone_256 took 187.5 ms at degree 3 and 70.9 ms at degree 0
+// (1.43e11 and 3.79e10 VALU instructions); with the batches and the plain slab
+// test for tables without axis-parallel lines 153 and 46.1 ms (1.27e11 and
+// 2.3e10, half the scalar ones), with the bricks dealt to the XCDs (xcd_remap)
+// 143 and 41.6; bit for bit the same sums.
 //
 // The table between the passes holds, per block, the FP64 parts of the
 // coefficients whose support meets its cells (11 x 11 x 7 for 8 x 8 x 4 cells
