@@ -76,7 +76,7 @@ TRAFFIC_BYTES = {  # (kernel, degree) -> (read bytes, written bytes) per applica
     ("project_kernel", 3): (2.0 * 4318666 * 1024, 1.0 * 281880 * 1024),
     ("backproject_cells_kernel", 3): (2.0 * 3169822 * 1024, 1.0 * 468950 * 1024),
     ("cells_to_coeffs_kernel", 3): (2.0 * 521261 * 1024, 1.0 * 65536 * 1024),
-    ("pad_volume_zfast_kernel", 0): (2.0 * 65557 * 1024, 1.0 * 72242 * 1024),
+    ("pad_volume_zfast_kernel", 0): (2.0 * 65562 * 1024, 1.0 * 80001 * 1024),
     ("pad_volume_kernel", 0): (2.0 * 36889 * 1024, 1.0 * 67084 * 1024),
     ("project_kernel", 0): (2.0 * 3473543 * 1024, 1.0 * 289296 * 1024),
     ("backproject_cells_kernel", 0): (2.0 * 3136521 * 1024, 1.0 * 65536 * 1024),
